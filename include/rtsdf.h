@@ -420,7 +420,7 @@ void rtsdf_scene_destroy(rtsdf_scene *scene);
 /*            rays of each persistent wavefront's tile (drawn, then sorted   */
 /*            by direction bin), and the spill area of the traversal stacks  */
 /*            (entries deeper than the LDS part, for hierarchies up to depth */
-/*            64); ~310 MB on a 256-CU device (the size is that of the       */
+/*            64); ~320 MB on a 256-CU device (the size is that of the       */
 /*            current device).  Calls that run                               */
 /*            concurrently need separate workspaces; they may trace the same */
 /*            scene.                                                         */
@@ -473,13 +473,16 @@ int rtsdf_trace_accumulate(const rtsdf_scene *scene, rtsdf_grid coarse, const fl
  *                   their wavefront; each time 64 tests are queued, every
  *                   lane takes one (of any lane's ray); traversals cull
  *                   with their ray's best distance as of the last queue
- *                   flush.  Two-level scenes, 4-wide traversals and scenes
+ *                   flush, and start at the subtrees that rays from their
+ *                   tile can meet instead of at the root.  Two-level scenes, 4-wide traversals and scenes
  *                   of 2^26 or more triangle references use 3 instead;
  *                   default 4;
  *   bin_directions  1: each wavefront's tile of rays is sorted by direction
  *                   before tracing (coherence); 0: queue order;
  *   stack_lds       traversal stack entries kept in LDS per lane (12, 16 or
- *                   24); deeper entries go to the workspace's spill area;
+ *                   24; the queued loop keeps four fewer, whose place its
+ *                   entry points take); deeper entries go to the workspace's
+ *                   spill area;
  *   tile_texels     texels per wavefront tile at most (16, 32 or 64; a tile
  *                   also holds at most 768 rays, i.e. 768 / rays texels);
  *   bvh_width       2: traverse the two-child hierarchy; 4: a 4-wide copy of

@@ -24,6 +24,11 @@
 // crosses a shared edge hits at least one of its triangles.  Ties in t go to
 // the lower triangle index; t must be > 0.
 //
+// Entry points: the rays of a tile start in one small block, so the upper
+// levels of the hierarchy are the same work for all of them.  The queued loop
+// opens those levels once per tile (tile_setup) and starts each ray from the
+// subtrees it can meet.
+//
 // Work distribution: persistent wavefronts; one lane owns one selected texel
 // and traces its rays one after another.  Lanes whose texel is finished are
 // refilled from the compacted queue by one atomic add per wavefront (ballot +
@@ -37,6 +42,18 @@ namespace rtsdf {
 
 // ------------------------------------------------------------------ RNG ----
 
+// a * b in full: four 32-bit multiply-adds whose partial sums serve both halves (a product per half, from
+// __umul64hi and *, repeats the cross products: 7 multiplies)
+__device__ __forceinline__ void mul_wide(uint64_t a, uint64_t b, uint64_t &hi, uint64_t &lo)
+{
+    const uint32_t a0 = (uint32_t)a, a1 = (uint32_t)(a >> 32), b0 = (uint32_t)b, b1 = (uint32_t)(b >> 32);
+    const uint64_t p00 = (uint64_t)a0 * b0;
+    const uint64_t p10 = (uint64_t)a1 * b0 + (p00 >> 32);
+    const uint64_t p01 = (uint64_t)a0 * b1 + (uint32_t)p10;
+    hi = (uint64_t)a1 * b1 + (p10 >> 32) + (p01 >> 32);
+    lo = (p01 << 32) | (uint32_t)p00;
+}
+
 __device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64_t k1)
 {
     const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
@@ -47,8 +64,9 @@ __device__ __forceinline__ void philox4x64_10(uint64_t c[4], uint64_t k0, uint64
             k0 += W0;
             k1 += W1;
         }
-        const uint64_t hi0 = __umul64hi(M0, c[0]), lo0 = M0 * c[0];
-        const uint64_t hi1 = __umul64hi(M1, c[2]), lo1 = M1 * c[2];
+        uint64_t hi0, lo0, hi1, lo1;
+        mul_wide(M0, c[0], hi0, lo0);
+        mul_wide(M1, c[2], hi1, lo1);
         const uint64_t y0 = hi1 ^ c[1] ^ k0, y2 = hi0 ^ c[3] ^ k1;
         c[0] = y0;
         c[1] = lo1;
@@ -67,15 +85,23 @@ __device__ __forceinline__ float3 sphere_dir(uint64_t seed, uint32_t texel, uint
     for (uint32_t attempt = 0; attempt < 8; ++attempt) {
         uint64_t c[4] = {(uint64_t)texel, ((uint64_t)frame << 32) | ray, (uint64_t)scene, (uint64_t)attempt};
         philox4x64_10(c, seed, 0);
-        for (int p = 0; p < 4; ++p) {
-            const float x1 = uniform_pm1((uint32_t)c[p]);
-            const float x2 = uniform_pm1((uint32_t)(c[p] >> 32));
-            const float s = rn_add(rn_mul(x1, x1), rn_mul(x2, x2));
-            if (s < 1.0f) {
-                const float q = rn_sqrt(rn_sub(1.0f, s));
-                return make_float3(rn_mul(rn_mul(2.0f, x1), q), rn_mul(rn_mul(2.0f, x2), q),
-                                   rn_sub(1.0f, rn_mul(2.0f, s)));
-            }
+        // the first of the four pairs inside the disc (without branches: some lane of a wavefront needs the third
+        // or fourth pair nearly every time)
+        float x1 = 0.0f, x2 = 0.0f, s = 2.0f;
+#pragma unroll
+        for (int p = 3; p >= 0; --p) {
+            const float y1 = uniform_pm1((uint32_t)c[p]);
+            const float y2 = uniform_pm1((uint32_t)(c[p] >> 32));
+            const float t = rn_add(rn_mul(y1, y1), rn_mul(y2, y2));
+            const bool in = t < 1.0f;
+            x1 = in ? y1 : x1;
+            x2 = in ? y2 : x2;
+            s = in ? t : s;
+        }
+        if (s < 1.0f) {
+            const float q = rn_sqrt(rn_sub(1.0f, s));
+            return make_float3(rn_mul(rn_mul(2.0f, x1), q), rn_mul(rn_mul(2.0f, x2), q),
+                               rn_sub(1.0f, rn_mul(2.0f, s)));
         }
     }
     return make_float3(0.0f, 0.0f, 1.0f);
@@ -349,7 +375,8 @@ struct TraceArgs {
     int spill_stride;            // lanes in the launch
     int bin_directions;          // sort each tile's rays by direction bin
     int tile_cap;                // texels per wavefront tile at most (16, 32 or 64)
-    float4 *dirs;                // per wavefront: kTileRays directions of its current tile
+    int few_rays;                // queued loop without entry points (see kFewRays)
+    float4 *dirs;                // per wavefront: kTileRays directions, then kTileRays records in bin order
 };
 
 constexpr int kTraceWaves = 4;
@@ -369,6 +396,13 @@ typedef __attribute__((address_space(3))) int lds_int;
 __device__ __forceinline__ const BvhNode *node_ptr(const BvhNode *base, int node)
 {
     return reinterpret_cast<const BvhNode *>(reinterpret_cast<const char *>(base) + (uint32_t)node * 64u);
+}
+
+// the same record read through the scalar cache (wave-uniform node index)
+typedef __attribute__((address_space(4))) const float sfloat;
+__device__ __forceinline__ const sfloat *node_sptr(const BvhNode *base, int node)
+{
+    return (const sfloat *)(reinterpret_cast<uintptr_t>(base) + (uintptr_t)(uint32_t)node * 64u);
 }
 
 __device__ __forceinline__ const float4 *tri_ptr(const float4 *base, int tri)
@@ -561,8 +595,8 @@ __device__ __forceinline__ void node_step_flat(const BvhView &S, const RaySetup 
 constexpr int kBins = 64;
 __device__ __forceinline__ int direction_bin(float3 d)
 {
-    const float s = fabsf(d.x) + fabsf(d.y) + fabsf(d.z);
-    float u = d.x / s, v = d.y / s;
+    const float s = __builtin_amdgcn_rcpf(fabsf(d.x) + fabsf(d.y) + fabsf(d.z));  // (a bin only orders the rays)
+    float u = d.x * s, v = d.y * s;
     if (d.z < 0.0f) {
         const float uu = (1.0f - fabsf(v)) * (u >= 0.0f ? 1.0f : -1.0f);
         const float vv = (1.0f - fabsf(u)) * (v >= 0.0f ? 1.0f : -1.0f);
@@ -581,11 +615,65 @@ constexpr int kMaxQueuedRefs = 1 << 26;  // queue entries: leaf-order index << 6
 static_assert(2 * kWave <= kQueueCap && (kQueueCap & (kQueueCap - 1)) == 0, "queue size");
 static_assert(kBins <= kQueueCap, "the bin counters share the queue's words");
 
+// Entry points of a tile at most: the bits of two mask words, the last of which marks the end.  At 31, 46 and 62 the
+// room (216k triangles, 128^3 / 256^3, 16 rays) traces in 22.4, 21.5 and 21.1 ms and visits 17.9, 15.3 and 13.1 nodes a
+// ray, against 28.0 ms and 34.3 without entry points; each entry point costs one box test per ray, at full width.
+constexpr int kEntries = 62;
+constexpr int kEntryEnd = 63;
+constexpr int kEntryStack = 4;  // stack entries per lane whose LDS the two contexts' entry points take
+// A node is opened while its box's half area over the squared distance to it from the tile's block (plus the block's
+// half diagonal squared) exceeds kOpen: about the chance that a ray meets it, times 8 pi.  4 (one ray in six) and 8 are
+// within 0.3 %, 16 costs the smaller scenes 3 %.  kOpenTogether: a round opens every node above this share of the
+// round's largest such value, so that the nodes that matter most are open when the 62 run out (0.25: 2 % slower; one
+// node at a time, 61 rounds instead of about 25: 4 % slower; all above kOpen: 20 % slower).
+constexpr float kOpen = 4.0f, kOpenTogether = 0.5f;
+// Tiles of at most this many rays start at the root (loop shape 5, chosen at launch): choosing entry points, and
+// their place in the traversal loop, cost more than the node visits they save.  With entry points, 64 texels x 1 ray
+// trace 2 to 4 % slower (room-like scene, 128^3 / 256^3: 2,206 against 2,284 us an update), x 2 rays 1.5 % slower, x 3
+// rays 9 % faster (4,243 against 3,864 us).
+constexpr int kFewRays = 128;
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) v4f gv4f;
+typedef __attribute__((address_space(1))) v2u gv2u;
+typedef __attribute__((address_space(1))) const int32_t gint;
+
+// Maxima over the wavefront's 64 lanes of N unsigned values, as scalars (data-parallel-primitive steps within rows of
+// 16 lanes, then across rows; the values' chains are interleaved).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+}
+template <int N>
+__device__ __forceinline__ void wave_umax(uint32_t (&v)[N])
+{
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = max(v[k], dpp_or_zero<0x111>(v[k]));  // row_shr 1, 2, 4, 8
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = max(v[k], dpp_or_zero<0x112>(v[k]));
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = max(v[k], dpp_or_zero<0x114>(v[k]));
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = max(v[k], dpp_or_zero<0x118>(v[k]));
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = max(v[k], dpp_or_zero<0x142>(v[k]));  // row_bcast 15, 31
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = max(v[k], dpp_or_zero<0x143>(v[k]));
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = (uint32_t)__builtin_amdgcn_readlane((int)v[k], 63);
+}
+
 // A wavefront's LDS: the texel results of two tile contexts (the tile whose rays are handed out and the one
 // before it, whose last rays may still be in flight; context c holds entries c * kTileTexels + slot), each
 // lane's best hit key (queued loop) and the triangle-test queue, whose words hold the direction-bin counters
 // while a tile's rays are sorted (the queue is empty then).
+template <bool ENTRIES>
 struct WaveTile {
+    // per context: the entry points of its rays (child code, bits of the least distance to it), nearest first
+    v2i entry[ENTRIES ? 2 * (kEntryEnd + 1) : 1];
     int32_t tex[2 * kTileTexels];
     unsigned long long key[2 * kTileTexels];  // min over rays of (distance bits << 32 | ray << 26 | triangle)
     uint32_t cnt[2 * kTileTexels];            // front | back << 16 for this frame
@@ -595,6 +683,291 @@ struct WaveTile {
         uint32_t bin[kBins];         // bin counts, then bin cursors
     };
 };
+
+template <bool ENTRIES>
+using lds_tile = __attribute__((address_space(3))) WaveTile<ENTRIES>;
+typedef __attribute__((address_space(3))) v2i lds_v2i;
+typedef __attribute__((address_space(4))) const TraceScene *scene_ptr;
+static_assert(offsetof(TraceArgs, one) == 0, "a single scene's record is read at the start of the kernel arguments");
+
+__device__ __forceinline__ uint64_t uniform64(uint64_t x)
+{
+    return (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32)) << 32 |
+           (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+}
+
+// the next entry point of a ray (child code); kDone when none is left, or when the next one, and so every later one,
+// lies beyond the ray's best distance
+struct EntryCursor {
+    uint32_t m0, m1;     // entry points not yet visited: the current word, the next one
+    const lds_v2i *tab;  // the current word's table
+};
+__device__ __forceinline__ int entry_pop(EntryCursor &E, float tbest)
+{
+    if (E.m0 == 0u) {
+        E.m0 = E.m1;
+        E.tab += 32;
+    }
+    const v2i e = E.tab[__builtin_ctz(E.m0)];
+    E.m0 &= E.m0 - 1u;
+    return tbest < __int_as_float(e.y) ? kDone : e.x;
+}
+
+// Sets up a tile of rays in a wavefront's context c: draws the directions, sorts the rays by direction bin into
+// records, and (ENTRIES) chooses the tile's entry points and which of them each ray meets.
+//
+// Entry points: starting from the root, the nodes most likely to be met by rays from the tile's block are replaced by
+// their children (lane k holds entry point k), so every ray starts at the subtrees it meets, nearest first, instead of
+// descending through the levels above them: half to two thirds of its node visits, each a fetch of scattered records
+// and a step at partial width, become box tests at full width whose boxes come by the scalar cache.  Which rays meet an
+// entry point is decided 64 sorted records at a time: lane k first tests entry point k against the bounds of the 64
+// directions, and only those it may concern are tested ray by ray.  A box's slab test holds whenever that of a box
+// inside it does, so the leaves a ray reaches are those it reaches from the root.
+//
+// Not inlined: its registers (41) are then not the traversal loop's (80: six wavefronts per SIMD), and the loop's state
+// is saved once per tile.  Inlined, both spilled (a batch's loop reloaded 24 registers each round, 24.1 against 17.8 ms
+// per step on 12 scenes).  Arguments arrive in vector registers and are made scalar here.  Its cost is bound by vector
+// instructions: about 1,400 per 64 rays, half of them the generator's.
+template <bool ENTRIES>
+__device__ __noinline__ void tile_setup(scene_ptr P_, lds_tile<ENTRIES> *T_, gv4f *dirs_, int base_, int nt_, int c_,
+                                        uint64_t seed_, uint32_t frame_, int bin_directions_)
+{
+    const scene_ptr P = (scene_ptr)uniform64((uint64_t)P_);
+    lds_tile<ENTRIES> *T =
+        (lds_tile<ENTRIES> *)(uintptr_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)T_);
+    gv4f *dirs = (gv4f *)uniform64((uint64_t)dirs_);
+    gv4f *recs = dirs + kTileRays;
+    const int base = __builtin_amdgcn_readfirstlane(base_), nt = __builtin_amdgcn_readfirstlane(nt_);
+    const int c = __builtin_amdgcn_readfirstlane(c_), bin_directions = __builtin_amdgcn_readfirstlane(bin_directions_);
+    const uint64_t seed = uniform64(seed_);
+    const uint32_t frame = (uint32_t)__builtin_amdgcn_readfirstlane((int)frame_);
+    const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    // q / R as a multiply-high, as in the tracer
+    const int R = P->rays, nrays = nt * R, lognf = P->lognf, qm = P->nf - 1;
+    const uint32_t rdiv = R > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)R - 1) / (uint64_t)R) : 0u;
+    const float lox = P->lox, loy = P->loy, loz = P->loz, hf = P->hf;
+    const BvhNode *nodes = P->bvh.nodes;
+    const uint64_t ntex_grid = (uint64_t)1 << (3 * lognf);
+    const int c0 = c * kTileTexels;
+    int jt = -1;
+    if (lane < nt) {
+        jt = ((gint *)(uintptr_t)P->queue)[base + lane];
+        if (jt < 0 || (uint64_t)jt >= ntex_grid) jt = -1;
+        T->tex[c0 + lane] = jt;
+        T->key[c0 + lane] = ~0ull;
+        T->cnt[c0 + lane] = 0u;
+    }
+    T->bin[lane] = 0u;  // the queue is empty between traversal rounds
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // ---- bin the tile's rays by direction (the bin rides in the direction record's w)
+    const uint32_t scene_id = P->scene_id;
+#pragma unroll 1
+    for (int q = lane; q < nrays; q += kWave) {
+        const int qs = R > 1 ? (int)__umulhi((uint32_t)q, rdiv) : q, qr = q - qs * R;
+        const int j = T->tex[c0 + qs];
+        int b = 0;
+        if (j >= 0) {
+            // drawn once at full width; the lane that later takes the ray reads it back
+            const float3 d = sphere_dir(seed, (uint32_t)j, frame, (uint32_t)qr, scene_id);
+            if (bin_directions) b = direction_bin(d);
+            dirs[q] = v4f{d.x, d.y, d.z, __int_as_float(b)};
+        }
+        __hip_atomic_fetch_add(&T->bin[b], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    {  // exclusive scan of the 64 bin counts, one per lane
+        const uint32_t cb = T->bin[lane];
+        uint32_t x = cb;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off);
+            if (lane >= off) x += y;
+        }
+        T->bin[lane] = x - cb;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    // ---- the records in bin order (each lane re-reads the directions it stored)
+#pragma unroll 1
+    for (int q = lane; q < nrays; q += kWave) {
+        const int qs = R > 1 ? (int)__umulhi((uint32_t)q, rdiv) : q;
+        v4f d = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        if (T->tex[c0 + qs] >= 0) d = dirs[q];
+        const uint32_t pos = __hip_atomic_fetch_add(&T->bin[__float_as_int(d.w)], 1u, __ATOMIC_RELAXED,
+                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
+        d.w = __int_as_float(q);
+        recs[pos] = d;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // also orders the stored records
+    __builtin_amdgcn_wave_barrier();
+    if constexpr (ENTRIES) {
+        gv2u *masks = (gv2u *)dirs;
+        lds_v2i *entry = T->entry + c * (kEntryEnd + 1);
+        if (lane == 0) entry[kEntryEnd] = v2i{kDone, 0};
+        if (P->nt == 0) {  // nothing to meet
+            for (int i = lane; i < nrays; i += kWave) masks[i] = v2u{0u, 0u};
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            return;
+        }
+        // ---- the tile's entry points
+        uint32_t bb[6] = {0u, 0u, 0u, 0u, 0u, 0u};
+        if (jt >= 0) {
+            const uint32_t x = (uint32_t)(jt & qm), y = (uint32_t)((jt >> lognf) & qm);
+            const uint32_t z = (uint32_t)(jt >> (2 * lognf));
+            bb[0] = 2047u - x;
+            bb[1] = x;
+            bb[2] = 2047u - y;
+            bb[3] = y;
+            bb[4] = 2047u - z;
+            bb[5] = z;
+        }
+        wave_umax<6>(bb);
+        const float bx0 = texel_coord(lox, (int)(2047u - bb[0]), hf), bx1 = texel_coord(lox, (int)bb[1], hf);
+        const float by0 = texel_coord(loy, (int)(2047u - bb[2]), hf), by1 = texel_coord(loy, (int)bb[3], hf);
+        const float bz0 = texel_coord(loz, (int)(2047u - bb[4]), hf), bz1 = texel_coord(loz, (int)bb[5], hf);
+        // rounding of the block's differences with box planes (box padding covers it unless the grid lies far outside)
+        const float slack = 0x1p-21f * (fabsf(bx0) + fabsf(bx1) + fabsf(by0) + fabsf(by1) + fabsf(bz0) + fabsf(bz1));
+        const float ex = bx1 - bx0 + hf, ey = by1 - by0 + hf, ez = bz1 - bz0 + hf;
+        const float s2 = 0.25f * (ex * ex + ey * ey + ez * ez);
+        // lane k holds entry point k: child code, its box's place (node << 1 | slot), priority, squared distance
+        int nentry = 1, ecode = lane < nentry ? 0 : kDone, eref = 0;
+        float eprio = 1e30f, ed2 = 0.0f;
+        const int cap = min(kEntries, 14 + (nrays >> 4));
+        while (true) {
+            const int room = cap - nentry;
+            uint32_t top[1] = {ecode >= 0 ? __float_as_uint(eprio) : 0u};
+            wave_umax<1>(top);
+            float tau = kOpenTogether * __uint_as_float(top[0]);
+            if (!(__uint_as_float(top[0]) > kOpen) || room <= 0) break;
+            uint64_t want = __builtin_amdgcn_ballot_w64(ecode >= 0 && eprio > fmaxf(tau, kOpen));
+            while (__popcll(want) > room) {
+                tau *= 1.25f;
+                want = __builtin_amdgcn_ballot_w64(ecode >= 0 && eprio > fmaxf(tau, kOpen));
+            }
+            if (want == 0) break;
+            const bool op = (want >> lane) & 1;
+            gv4f *nd = (gv4f *)((uintptr_t)nodes + (uintptr_t)(uint32_t)(op ? ecode : 0) * 64u);
+            const v4f a = nd[0], b = nd[1], z = nd[2], m = nd[3];
+            const auto eval = [&](float lx, float hx, float ly, float hy, float lz, float hz, float &prio, float &d2) {
+                const float dx = fmaxf(fmaxf(lx - bx1, bx0 - hx), 0.0f);
+                const float dy = fmaxf(fmaxf(ly - by1, by0 - hy), 0.0f);
+                const float dz = fmaxf(fmaxf(lz - bz1, bz0 - hz), 0.0f);
+                const float wx = hx - lx, wy = hy - ly, wz = hz - lz;
+                d2 = dx * dx + dy * dy + dz * dz;
+                prio = (wx * wy + wy * wz + wz * wx) * __builtin_amdgcn_rcpf(d2 + s2);
+            };
+            float p0, q0, p1, q1;
+            eval(a.x, a.y, a.z, a.w, z.x, z.y, p0, q0);
+            eval(b.x, b.y, b.z, b.w, z.z, z.w, p1, q1);
+            const int m0 = __float_as_int(m.x), m1 = __float_as_int(m.y), parent = ecode;
+            const bool two = op && !(m1 < 0 && leaf_count(m1) == 0);  // (a one-leaf scene has an empty second leaf)
+            const uint64_t twos = __builtin_amdgcn_ballot_w64(two);
+            if (two)
+                T->q[__builtin_amdgcn_mbcnt_hi((uint32_t)(twos >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)twos, 0u))] =
+                    (uint32_t)lane;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int added = (int)__popcll(twos);
+            const bool isnew = lane >= nentry && lane < nentry + added;
+            const int src = isnew ? (int)T->q[lane - nentry] << 2 : 0;
+            const int n_code = __builtin_amdgcn_ds_bpermute(src, m1);
+            const int n_parent = __builtin_amdgcn_ds_bpermute(src, parent);
+            const float n_prio = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(p1)));
+            const float n_d2 = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(q1)));
+            if (op) {
+                ecode = m0;
+                eref = parent << 1;
+                eprio = p0;
+                ed2 = q0;
+            }
+            if (isnew) {
+                ecode = n_code;
+                eref = n_parent << 1 | 1;
+                eprio = n_prio;
+                ed2 = n_d2;
+            }
+            nentry += added;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+        // nearest first; of those that the block touches, the smallest first
+        float eord = ed2 > 0.0f ? ed2 : -__builtin_amdgcn_rcpf(eprio);
+        if (!(eord == eord)) eord = 0.0f;  // (the ranks have to be distinct)
+        int rank = 0;
+        for (int k = 0; k < nentry; ++k) {
+            const float ok = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(eord), k));
+            rank += ok < eord || (ok == eord && k < lane);
+        }
+        if (lane < nentry) {
+            const float least = 0.9999f * __builtin_amdgcn_sqrtf(ed2) - slack;
+            entry[rank] = v2i{ecode, __float_as_int(least)};
+            T->q[rank] = (uint32_t)eref;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        eref = lane < nentry ? (int)T->q[lane] : 0;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // ---- which entry points each ray meets, 64 records (similar directions) at a time
+        gv4f *en = (gv4f *)((uintptr_t)nodes + (uintptr_t)(uint32_t)(eref >> 1) * 64u);
+        const v4f exy = en[eref & 1], ezz = en[2];
+        const float elz = eref & 1 ? ezz.z : ezz.x, ehz = eref & 1 ? ezz.w : ezz.y;
+        const float Lx = exy.x - bx1 - slack, Hx = exy.y - bx0 + slack, Ly = exy.z - by1 - slack,
+                    Hy = exy.w - by0 + slack, Lz = elz - bz1 - slack, Hz = ehz - bz0 + slack;
+    #pragma unroll 1
+        for (int i0 = 0; i0 < nrays; i0 += kWave) {
+            const int i = i0 + lane;
+            const v4f d = recs[min(i, nrays - 1)];
+            const int q = __float_as_int(d.w), qs = R > 1 ? (int)__umulhi((uint32_t)q, rdiv) : q;
+            const int j = T->tex[c0 + qs];
+            RaySetup Q;
+            ray_setup(texel_coord(lox, j & qm, hf), texel_coord(loy, (j >> lognf) & qm, hf),
+                      texel_coord(loz, j >> (2 * lognf), hf), d.x, d.y, d.z, Q);
+            // lane k: whether a ray from the tile's block, its direction in these 64 rays' bounds, can meet entry point k
+            uint32_t db[6] = {__float_as_uint(2.0f - d.x), __float_as_uint(2.0f + d.x), __float_as_uint(2.0f - d.y),
+                              __float_as_uint(2.0f + d.y), __float_as_uint(2.0f - d.z), __float_as_uint(2.0f + d.z)};
+            wave_umax<6>(db);
+            float t0 = 0.0f, t1 = __builtin_inff();
+            const auto axis = [&](uint32_t lo, uint32_t hi, float L, float H) {
+                const float d0 = 1.999999f - __uint_as_float(lo), d1 = __uint_as_float(hi) - 1.999999f;
+                const float i0 = __builtin_amdgcn_rcpf(d0), i1 = __builtin_amdgcn_rcpf(d1);
+                if (L > 0.0f) t0 = fmaxf(t0, d1 > 0.0f ? L * i1 : __builtin_inff());
+                if (H < 0.0f) t0 = fmaxf(t0, d0 < 0.0f ? H * i0 : __builtin_inff());
+                if (d0 > 0.0f) t1 = fminf(t1, H * i0);
+                if (d1 < 0.0f) t1 = fminf(t1, L * i1);
+            };
+            axis(db[0], db[1], Lx, Hx);
+            axis(db[2], db[3], Ly, Hy);
+            axis(db[4], db[5], Lz, Hz);
+            uint64_t cand = __builtin_amdgcn_ballot_w64(lane < nentry && !(t0 * 0.9999f > t1 * 1.0001f));
+            v2u mask = v2u{0u, 0u};
+            const auto meet = [&](int k) {
+                const int ref = __builtin_amdgcn_readlane(eref, k);
+                const sfloat *xy = node_sptr(nodes, ref >> 1) + 4 * (ref & 1);
+                const sfloat *zz = node_sptr(nodes, ref >> 1) + 8 + 2 * (ref & 1);
+                float te;
+                return box_hit(Q, xy[0], xy[1], xy[2], xy[3], zz[0], zz[1], __builtin_inff(), te);
+            };
+            uint32_t c0w = (uint32_t)cand, c1w = (uint32_t)(cand >> 32);
+            while (c0w) {
+                const int k = __builtin_ctz(c0w);
+                c0w &= c0w - 1u;
+                if (meet(k)) mask.x |= 1u << k;
+            }
+            while (c1w) {
+                const int k = __builtin_ctz(c1w);
+                c1w &= c1w - 1u;
+                if (meet(32 + k)) mask.y |= 1u << k;
+            }
+            if (i < nrays) masks[i] = j >= 0 ? mask : v2u{0u, 0u};
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
 
 // Tiles of a scene: ceil(min(count, cap) / tile texels).
 __device__ __forceinline__ int scene_tiles(const TraceScene &P, int cap)
@@ -650,22 +1023,25 @@ __global__ void trace_tile_prefix(const TraceScene *scenes, int n, int cap, int3
 // visits that entered neither child box (LOOP 3), tiles started while lanes
 // were still busy x 64, traversal rounds that waited for every lane before a
 // next tile x 64.
-template <int SL, int REFILL, int LOOP, bool STATS, bool BATCHED, bool INST = false, bool WIDE = false>
+template <int STACK, int REFILL, int LOOP, bool STATS, bool BATCHED, bool INST = false, bool WIDE = false>
 __global__ void __launch_bounds__(kTraceWaves * kWave) __attribute__((amdgpu_waves_per_eu(6, 8)))
 trace_persistent(TraceArgs A)
 {
     uint32_t st_nodes = 0, st_tris = 0, st_rays = 0, st_iters = 0, st_refills = 0, st_busy = 0, st_tiles = 0;
     uint32_t st_empty = 0, st_early = 0, st_drains = 0;
+    constexpr bool QUEUED = LOOP >= 4, ENTRIES = LOOP == 4;
+    constexpr int SL = ENTRIES ? STACK - kEntryStack : STACK;  // stack entries per lane in LDS
     __shared__ int stack_mem[kTraceWaves * SL * kWave];
-    __shared__ WaveTile tiles[kTraceWaves];
+    __shared__ WaveTile<ENTRIES> tiles[kTraceWaves];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     lds_int *stk = (lds_int *)(stack_mem + wave * SL * kWave + lane);
-    WaveTile &T = tiles[wave];
+    WaveTile<ENTRIES> &T = tiles[wave];
     int32_t *spill = A.spill + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     // the wavefront's two direction buffers: by ray id (slot * R + ray), and the same rays in bin order as
     // (direction, ray id) records
     float4 *dirs = A.dirs + ((int64_t)blockIdx.x * kTraceWaves + wave) * (2 * kTileRays);
     float4 *recs = dirs + kTileRays;
+    gv2u *masks = (gv2u *)(uintptr_t)dirs;  // the records' entry points (the drawn directions are read by then)
     const int stride = A.spill_stride;
     const uint32_t frame = A.frame_ptr ? *A.frame_ptr : A.frame;
     if (frame >= kMaxFrame) {
@@ -699,6 +1075,7 @@ trace_persistent(TraceArgs A)
     int ibest = -1, node = kDone, leaf = kDone, sp = 0;
     int tri_cur = 0, tri_end = 0;
     bool front = false;
+    EntryCursor E{0u, 0u, nullptr};  // queued loop: the entry points not yet visited (bit kEntryEnd: none left)
 
     while (true) {
         // ---- start the next tile once the current one has handed out its last ray
@@ -727,58 +1104,11 @@ trace_persistent(TraceArgs A)
                 const int total = min(*P.count, P.queue_cap);
                 const int base = (g - (BATCHED ? A.tile_offset[sn] : 0)) * tile_texels;
                 const int nt = min(tile_texels, total - base);
-                const uint64_t ntex_grid = (uint64_t)1 << (3 * P.lognf);
-                const int c0 = c * kTileTexels;
-                if (lane < nt) {
-                    int j = P.queue[base + lane];
-                    if (j < 0 || (uint64_t)j >= ntex_grid) j = -1;
-                    T.tex[c0 + lane] = j;
-                    T.key[c0 + lane] = ~0ull;
-                    T.cnt[c0 + lane] = 0u;
-                }
-                T.bin[lane] = 0u;  // the queue is empty between traversal rounds
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                // ---- bin the tile's rays by direction (the bin rides in the direction record's w)
+                const scene_ptr sp4 = BATCHED ? (scene_ptr)(uintptr_t)(A.scenes + sn)
+                                              : (scene_ptr)__builtin_amdgcn_kernarg_segment_ptr();
                 nrays = nt * R;
-#pragma unroll 1
-                for (int q = lane; q < nrays; q += kWave) {
-                    const int qs = R > 1 ? (int)__umulhi((uint32_t)q, rdiv) : q, qr = q - qs * R;
-                    const int j = T.tex[c0 + qs];
-                    int b = 0;
-                    if (j >= 0) {
-                        // drawn once at full width; the lane that later takes the ray reads it back
-                        const float3 d = sphere_dir(A.seed, (uint32_t)j, frame, (uint32_t)qr, P.scene_id);
-                        if (A.bin_directions) b = direction_bin(d);
-                        dirs[q] = make_float4(d.x, d.y, d.z, __int_as_float(b));
-                    }
-                    atomicAdd(&T.bin[b], 1u);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                {  // exclusive scan of the 64 bin counts, one per lane
-                    const uint32_t cb = T.bin[lane];
-                    uint32_t x = cb;
-#pragma unroll
-                    for (int off = 1; off < kWave; off <<= 1) {
-                        const uint32_t y = __shfl_up(x, off);
-                        if (lane >= off) x += y;
-                    }
-                    T.bin[lane] = x - cb;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                // ---- the records in bin order (each lane re-reads the directions it stored)
-#pragma unroll 1
-                for (int q = lane; q < nrays; q += kWave) {
-                    const int qs = R > 1 ? (int)__umulhi((uint32_t)q, rdiv) : q;
-                    float4 d = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if (T.tex[c0 + qs] >= 0) d = dirs[q];
-                    const uint32_t pos = atomicAdd(&T.bin[__float_as_int(d.w)], 1u);
-                    recs[pos] = make_float4(d.x, d.y, d.z, __int_as_float(q));
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // also orders the stored records
-                __builtin_amdgcn_wave_barrier();
+                tile_setup<ENTRIES>(sp4, (lds_tile<ENTRIES> *)&T, (gv4f *)(uintptr_t)dirs, base, nt, c, A.seed, frame,
+                                      A.bin_directions);
                 cstate[c] = nrays | nt << 16;
                 cscene[c] = sn;
                 cur = c;
@@ -815,9 +1145,16 @@ trace_persistent(TraceArgs A)
                         node = kDone;
                     }
                     tbest = __builtin_inff();
+                    if (ENTRIES) {
+                        const v2u m = masks[pool + rank];
+                        E.m0 = m.x;
+                        E.m1 = m.y | 1u << (kEntryEnd - 32);
+                        E.tab = ((lds_tile<ENTRIES> *)&T)->entry + cur * (kEntryEnd + 1);
+                        node = entry_pop(E, tbest);
+                    }
                     ibest = -1;
                     front = false;
-                    if (LOOP == 4) T.best[lane] = kBestInit;
+                    if (QUEUED) T.best[lane] = kBestInit;
                     leaf = kDone;
                     tri_cur = tri_end = 0;
                     sp = 0;
@@ -948,7 +1285,7 @@ trace_persistent(TraceArgs A)
                     const uint64_t done = wave_done(busy, node, tri_cur, tri_end);
                     if (__popcll(done) >= refill_at) break;
                 }
-            } else if (LOOP == 4) {
+            } else if (QUEUED) {
                 // Queued loop: a lane that reaches a leaf appends its triangles to the wavefront's queue
                 // in LDS (two per iteration at most) and goes on with its traversal; once a wavefront's
                 // worth of tests is queued, every lane takes one, whichever ray it belongs to, so the
@@ -1033,7 +1370,7 @@ trace_persistent(TraceArgs A)
                         pop = true;
                     }
                     if (push) stack_push<SL>(stride, sp, stk, spill, push_val);
-                    if (pop) node = stack_pop<SL>(stride, sp, stk, spill);
+                    if (pop) node = sp || !ENTRIES ? stack_pop<SL>(stride, sp, stk, spill) : entry_pop(E, tbest);
                     // ---- a wavefront's worth of tests
                     if (qt - qh >= kWave) flush(kWave);
                     const uint64_t done = wave_done(busy, node, tri_cur, tri_end);
@@ -1096,7 +1433,7 @@ trace_persistent(TraceArgs A)
             if (fin) {
                 if (STATS) ++st_rays;
                 int id = -1;
-                if (LOOP == 4) {
+                if (QUEUED) {
                     const unsigned long long kb = T.best[lane];
                     if (kb != kBestInit) {
                         tbest = __uint_as_float((uint32_t)(kb >> 32));
@@ -1310,7 +1647,7 @@ __global__ void __launch_bounds__(256) trace_backward_kernel(const float *__rest
 
 static rtsdf_trace_tuning g_tuning = {28, 0, 0, 4, 1, 12, 64, 2};
 constexpr int kMaxBlocksPerCu = 8;  // persistent workgroups per CU (direction buffers and spill area sized for this)
-constexpr int kMinShortStack = 12;  // smallest LDS stack part (spill area sized for this)
+constexpr int kMinShortStack = 12 - kEntryStack;  // smallest LDS stack part (spill area sized for this)
 constexpr int kMaxStackDepth = 64;  // deepest hierarchy the tracer takes
 
 static bool tuning_ok(const rtsdf_trace_tuning &t)
@@ -1359,7 +1696,9 @@ static int launch_trace3(const TraceArgs &A, const rtsdf_trace_tuning &T, hipStr
     case 0: return launch_trace4<SL, REFILL, 0, BATCHED>(A, T, s);
     case 1: return launch_trace4<SL, REFILL, 1, BATCHED>(A, T, s);
     case 2: return launch_trace4<SL, REFILL, 2, BATCHED>(A, T, s);
-    case 4: return launch_trace4<SL, REFILL, 4, BATCHED>(A, T, s);
+    case 4:
+        return A.few_rays ? launch_trace4<SL, REFILL, 5, BATCHED>(A, T, s)
+                          : launch_trace4<SL, REFILL, 4, BATCHED>(A, T, s);
     default: return launch_trace4<SL, REFILL, 3, BATCHED>(A, T, s);
     }
 }
@@ -1567,6 +1906,7 @@ extern "C" int rtsdf_trace_accumulate(const rtsdf_scene *scene, rtsdf_grid coars
     A.spill = ws_spill(workspace);
     A.spill_stride = 0;
     A.dirs = ws_dirs(workspace);
+    A.few_rays = tile_texels_for(rays_per_texel, T.tile_texels) * rays_per_texel <= kFewRays;
     if (scene->ninst > 0) return launch_trace_inst(A, T, s);
     return trace_wide(scene, T) ? launch_trace_wide(A, T, s) : launch_trace<false>(A, T, s);
 }
