@@ -7,13 +7,23 @@
 // column covered when its centre is inside or on the projected triangle, and
 // the voxel holding the triangle's depth at that centre marked.
 //
-// Work mapping: one lane per (triangle, axis), dealt to wavefronts with a
-// stride.  A lane rasterizes its own
-// projection when the bounding box holds at most kSmallPixels column centres;
-// larger projections (room walls cover whole faces of the grid) are flagged
-// and then rasterized by the whole wavefront, one after another, with the 64
-// lanes striding over the box, so a few huge triangles do not serialise one
-// lane.
+// Work mapping: a projection whose bounding box holds at most kSmallPixels
+// column centres is rasterized by one lane in 32-bit integers (three
+// projections a lane: a triangle's vertices are snapped once); larger ones by
+// a whole wavefront, and those of more than kWavePixels (room walls cover
+// whole faces of the grid) by the whole workgroup, in 64-bit integers.
+// Triangles are dealt to workgroups one by one, so the large projections of
+// consecutive triangles (the walls of a room come one after another) land in
+// different workgroups instead of queueing in one.
+//
+// Bound by the latency of its gathers and its largest projections: with the
+// fill of the seeds, 1.0 M triangles at 256^3 355 -> 151 us, 211 k at 128^3
+// 108 -> 48 us, 1,880 large ones at 256^3 432 -> 54 us, 322 at 32^3 16 -> 11 us
+// (against one lane per (triangle, axis) in 64-bit integers, which snapped each
+// vertex three times and left a wall's 65,536 columns to one wavefront).
+#include <algorithm>
+#include <cmath>
+
 #include "common.hpp"
 
 namespace rtsdf {
@@ -167,21 +177,152 @@ __device__ __forceinline__ void vox_wave_big(bool big, const VoxTri &T, int32_t 
     }
 }
 
-__global__ void __launch_bounds__(256) voxelize_kernel(const float *__restrict__ v, int nv,
-                                                       const int32_t *__restrict__ f, int nt, rtsdf_grid g,
-                                                       int32_t *__restrict__ seeds)
+// Threads per workgroup and fewest workgroups (four for each compute unit, so a small mesh's large projections do not
+// share one).  With 1024 threads a million triangles at 256^3 take 175 us, with 512 151, with 256 146, but 1,880 large
+// ones 54, 54 and 68; four consecutive triangles per workgroup (their faces in one cache line) 208 and 111.
+constexpr int kVoxThreads = 512;
+constexpr int kVoxBlocks = 1024;
+constexpr int kWavePixels = 512;   // largest projection a single wavefront takes
+constexpr int kSmallExtent = 8192;  // 32 voxels, also outside the grid: edge functions below 2^28 in 32 bits
+
+// A vertex snapped to 1/256 voxel; POW2: the voxel size is a power of two, so its inverse is exact and multiplies.
+template <bool POW2>
+__device__ __forceinline__ bool snap32(const float *__restrict__ v, const rtsdf_grid &g, double inv_h, int32_t X[3])
 {
-    // items are dealt to wavefronts with a stride (lane l of wavefront w takes item l * waves + w), so the
-    // large projections of consecutive triangles (the walls of a room come one after another) land in
-    // different wavefronts instead of queueing in one
-    const int64_t total = 3 * (int64_t)nt;
-    const int64_t waves = (total + kWave - 1) / kWave;
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t item = (gid & (kWave - 1)) * waves + (gid >> 6);
+    const double side = (double)g.n * (double)g.h;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double rel = (double)v[a] - (double)g.lo[a];
+        if (!(rel >= -side && rel <= 2.0 * side)) return false;
+        X[a] = (int32_t)__builtin_rint((POW2 ? rel * inv_h : rel / (double)g.h) * 256.0);
+    }
+    return true;
+}
+
+// One projection by one lane.  Returns true when it is left to more lanes: many columns, or long edges.
+__device__ __forceinline__ bool vox_small(const int32_t (&X)[3][3], int axis, int n, int32_t *__restrict__ seeds)
+{
+    const int e1 = (axis + 1) % 3, e2 = (axis + 2) % 3;
+    const int32_t x0 = X[0][e1], x1 = X[1][e1], x2 = X[2][e1], y0 = X[0][e2], y1 = X[1][e2], y2 = X[2][e2];
+    const int32_t minx = min(x0, min(x1, x2)), maxx = max(x0, max(x1, x2));
+    const int32_t miny = min(y0, min(y1, y2)), maxy = max(y0, max(y1, y2));
+    // column centre 256 i + 128 within [min, max]
+    const int i0 = max((minx + 127) >> 8, 0), i1 = min((maxx - 128) >> 8, n - 1);
+    const int j0 = max((miny + 127) >> 8, 0), j1 = min((maxy - 128) >> 8, n - 1);
+    if (i0 > i1 || j0 > j1) return false;
+    if (maxx - minx > kSmallExtent || maxy - miny > kSmallExtent || (i1 - i0 + 1) * (j1 - j0 + 1) > kSmallPixels)
+        return true;
+    int32_t area = (x1 - x0) * (y2 - y0) - (y1 - y0) * (x2 - x0);
+    if (area == 0) return false;
+    // edge functions times the orientation: all >= 0 inside or on the boundary, their sum |area|
+    const int32_t s = area < 0 ? -1 : 1;
+    area *= s;
+    const double den = (double)area * 256.0, inv = 1.0 / den;
+    const double z0 = X[0][axis], z1 = X[1][axis], z2 = X[2][axis];
+    const int sx = axis == 0 ? n : axis == 1 ? n * n : 1, sy = axis == 0 ? n * n : axis == 1 ? 1 : n;
+    const int sz = axis == 0 ? 1 : axis == 1 ? n : n * n;
+    for (int j = j0; j <= j1; ++j) {
+        const int32_t cy = 256 * j + 128;
+        for (int i = i0; i <= i1; ++i) {
+            const int32_t cx = 256 * i + 128;
+            const int32_t w0 = s * ((x2 - x1) * (cy - y1) - (y2 - y1) * (cx - x1));
+            const int32_t w1 = s * ((x0 - x2) * (cy - y2) - (y0 - y2) * (cx - x2));
+            const int32_t w2 = area - w0 - w1;
+            if ((w0 | w1 | w2) < 0) continue;
+            // depth num / den, every product and sum below 2^53: exact
+            const double num = (double)w0 * z0 + (double)w1 * z1 + (double)w2 * z2;
+            double L = floor(num * inv);  // off by at most one
+            const double rem = fma(-L, den, num);
+            if (rem < 0.0) L -= 1.0;
+            else if (rem >= den) L += 1.0;
+            if (num == (double)n * den) L = (double)(n - 1);
+            if (L < 0.0 || L >= (double)n) continue;
+            const int idx = (int)L * sz + i * sx + j * sy;
+            seeds[idx] = idx;
+        }
+    }
+    return false;
+}
+
+// One projection by many lanes: lane (lx, ly) of a block of 64 x ny columns.
+__device__ __forceinline__ void vox_wide(const int32_t (&X32)[3][3], int axis, int n, int lx, int ly, int ny,
+                                         int32_t *__restrict__ seeds)
+{
+    int64_t X[3][3];
+    for (int k = 0; k < 3; ++k)
+        for (int a = 0; a < 3; ++a) X[k][a] = X32[k][a];
     VoxTri T;
-    bool big = false;
-    if ((gid >> 6) < waves && item < total) big = vox_item(v, nv, f, (int)(item / 3), (int)(item % 3), g, seeds, T);
-    vox_wave_big(big, T, seeds, g.n);
+    if (!vox_setup(X, axis, n, T)) return;
+    for (int j = T.j0 + ly; j <= T.j1; j += ny)
+        for (int i = T.i0 + lx; i <= T.i1; i += kWave) vox_column(T, i, j, n, seeds);
+}
+
+template <bool POW2>
+__global__ void __launch_bounds__(kVoxThreads) voxelize_kernel(const float *__restrict__ v, int nv,
+                                                               const int32_t *__restrict__ f, int nt, rtsdf_grid g,
+                                                               double inv_h, int32_t *__restrict__ seeds)
+{
+    __shared__ uint32_t big[3 * kVoxThreads];  // projections left to the workgroup: thread << 2 | axis
+    __shared__ uint32_t nbig;
+    if (threadIdx.x == 0) nbig = 0u;
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    const auto tri_of = [&](uint32_t thread) { return (int64_t)thread * gridDim.x + blockIdx.x; };
+    const auto load = [&](int64_t t, int32_t (&X)[3][3]) {  // 0, or the error bit
+        for (int k = 0; k < 3; ++k) {
+            const int vi = f[3 * t + k];
+            if (vi < 0 || vi >= nv) return (uint32_t)RTSDF_ERR_FACE_INDEX;
+            X[k][0] = vi;
+        }
+        for (int k = 0; k < 3; ++k)
+            if (!snap32<POW2>(v + 3 * (int64_t)X[k][0], g, inv_h, X[k])) return (uint32_t)RTSDF_ERR_VERTEX_RANGE;
+        return 0u;
+    };
+    const int64_t t = tri_of(threadIdx.x);
+    int32_t X[3][3];
+    uint32_t wide = 0;  // axes left to the wavefront
+    if (t < nt) {
+        const uint32_t err = load(t, X);
+        if (err) raise_error(err);
+        else
+            for (int axis = 0; axis < 3; ++axis)
+                if (vox_small(X, axis, g.n, seeds)) {
+                    // columns of the box in the grid, as above
+                    const int e1 = (axis + 1) % 3, e2 = (axis + 2) % 3;
+                    const int w = min((max(X[0][e1], max(X[1][e1], X[2][e1])) - 128) >> 8, g.n - 1) -
+                                  max((min(X[0][e1], min(X[1][e1], X[2][e1])) + 127) >> 8, 0) + 1;
+                    const int h = min((max(X[0][e2], max(X[1][e2], X[2][e2])) - 128) >> 8, g.n - 1) -
+                                  max((min(X[0][e2], min(X[1][e2], X[2][e2])) + 127) >> 8, 0) + 1;
+                    if (w * h <= kWavePixels) wide |= 1u << axis;
+                    else big[atomicAdd(&nbig, 1u)] = threadIdx.x << 2 | (uint32_t)axis;
+                }
+    }
+    // the wavefront's projections, one after another
+    for (int axis = 0; axis < 3; ++axis) {
+        uint64_t pending = __ballot((wide >> axis & 1u) != 0u);
+        while (pending) {
+            const int src = __ffsll((unsigned long long)pending) - 1;
+            pending &= pending - 1;
+            int32_t B[3][3];
+            for (int k = 0; k < 3; ++k)
+                for (int a = 0; a < 3; ++a) B[k][a] = __builtin_amdgcn_readlane(X[k][a], src);
+            int64_t B64[3][3];
+            for (int k = 0; k < 3; ++k)
+                for (int a = 0; a < 3; ++a) B64[k][a] = B[k][a];
+            VoxTri T;
+            if (!vox_setup(B64, axis, g.n, T)) continue;
+            const int w = T.i1 - T.i0 + 1, npix = w * (T.j1 - T.j0 + 1);
+            for (int p = lane; p < npix; p += kWave) vox_column(T, T.i0 + p % w, T.j0 + p / w, g.n, seeds);
+        }
+    }
+    __syncthreads();
+    const uint32_t n = nbig;
+    for (uint32_t q = 0; q < n; ++q) {
+        const uint32_t e = big[q];
+        int32_t B[3][3];
+        (void)load(tri_of(e >> 2), B);  // (checked by its own lane)
+        vox_wide(B, (int)(e & 3u), g.n, lane, threadIdx.x >> 6, kVoxThreads / kWave, seeds);
+    }
 }
 
 }  // namespace rtsdf
@@ -198,8 +339,14 @@ extern "C" int rtsdf_voxelize(const float *vertices, int32_t nv, const int32_t *
     int rc = launch_fill<int32_t>(seeds, -1, nvox, s);
     if (rc != RTSDF_OK) return rc;
     if (nt == 0) return RTSDF_OK;
-    const int64_t items = 3 * (int64_t)nt;
-    voxelize_kernel<<<dim3((unsigned)((items + 255) / 256)), dim3(256), 0, s>>>(vertices, nv, faces, nt, coarse, seeds);
+    const int blocks = std::max((nt + kVoxThreads - 1) / kVoxThreads, std::min(nt, kVoxBlocks));
+    const dim3 grid((unsigned)blocks), block(kVoxThreads);
+    int e = 0;
+    const double inv_h = 1.0 / (double)coarse.h;
+    if (frexpf(coarse.h, &e) == 0.5f)  // a power of two
+        voxelize_kernel<true><<<grid, block, 0, s>>>(vertices, nv, faces, nt, coarse, inv_h, seeds);
+    else
+        voxelize_kernel<false><<<grid, block, 0, s>>>(vertices, nv, faces, nt, coarse, inv_h, seeds);
     RTSDF_CHECK_LAUNCH();
     return RTSDF_OK;
 }
