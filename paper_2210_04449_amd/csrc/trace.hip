@@ -391,6 +391,18 @@ __host__ __device__ __forceinline__ int tile_texels_for(int rays, int cap)
     return rays >= kTileRays ? 1 : min(cap, kTileRays / rays);
 }
 
+// Texels per tile of a single-scene launch.  A wavefront's time for N rays in tiles of r is about (N / r) (o + r), o
+// the cost of setting a tile up in rays, and the launch waits about one tile longer for the last wavefront: r = sqrt(o N) is
+// the best size while the launch is short.  o = 100 (30 to 200 measured): a 9 k-triangle mesh at 64^3 / 128^3 with 32
+// rays 5,890 -> 5,470 us for 6 updates, 230 k texels x 16 rays 841 -> 635 us, 87 k texels x 4 rays 234 -> 204 us; 734 k
+// texels x 4 rays 432 -> 438 us.  Whole records of 64 rays, at least two (one: 220 us for the last but one).
+__device__ __forceinline__ int tile_texels_auto(int rays, int cap, int total, int waves)
+{
+    const float r = __builtin_amdgcn_sqrtf(100.0f * (float)total * (float)rays / (float)waves);
+    const int n = max(2 * kWave, ((int)fminf(r, 2.0f * kTileRays) + kWave / 2) & ~(kWave - 1));
+    return max(1, min(tile_texels_for(rays, cap), n / rays));
+}
+
 typedef __attribute__((address_space(3))) int lds_int;
 
 __device__ __forceinline__ const BvhNode *node_ptr(const BvhNode *base, int node)
@@ -1050,7 +1062,9 @@ trace_persistent(TraceArgs A)
         if (blockIdx.x == 0 && threadIdx.x == 0) raise_error(RTSDF_ERR_FRAME);
         return;
     }
-    const int single_tiles = BATCHED ? 0 : scene_tiles(A.one, A.tile_cap);
+    const int one_total = BATCHED ? 0 : max(0, min(*A.one.count, A.one.queue_cap));
+    const int one_tt = BATCHED ? 1 : tile_texels_auto(A.one.rays, A.tile_cap, one_total, (int)gridDim.x * kTraceWaves);
+    const int single_tiles = BATCHED ? 0 : (one_total + one_tt - 1) / one_tt;
     const int all_tiles = BATCHED ? A.tile_offset[A.nscenes] : single_tiles;
     const auto scene_of = [&](int g) {  // last scene whose first tile is <= g
         int lo = 0, hi = A.nscenes - 1;
@@ -1100,7 +1114,7 @@ trace_persistent(TraceArgs A)
                 // q / R as a multiply-high: exact for q < kTileRays and R <= 64 (the error of the rounded-up
                 // reciprocal, q / 2^32, stays below the distance 1/R of q / R from the next integer)
                 rdiv = R > 1 ? (uint32_t)(((1ull << 32) + (uint64_t)R - 1) / (uint64_t)R) : 0u;
-                const int tile_texels = tile_texels_for(R, A.tile_cap);
+                const int tile_texels = BATCHED ? tile_texels_for(R, A.tile_cap) : one_tt;
                 const int total = min(*P.count, P.queue_cap);
                 const int base = (g - (BATCHED ? A.tile_offset[sn] : 0)) * tile_texels;
                 const int nt = min(tile_texels, total - base);
