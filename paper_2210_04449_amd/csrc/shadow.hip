@@ -15,6 +15,8 @@
 // Every float operation below is an explicitly rounded intrinsic in a fixed
 // order, so the march (including its data-dependent stopping decisions) is
 // reproducible exactly on another IEEE machine.
+#include <cmath>
+
 #include "common.hpp"
 
 namespace rtsdf {
@@ -22,10 +24,14 @@ namespace rtsdf {
 __device__ __forceinline__ float lerp_rn(float a, float b, float f) { return rn_add(a, rn_mul(f, rn_sub(b, a))); }
 
 // coordinate of q along one axis in texel-centre units, clamped to [0, n-1];
-// false if q is outside the grid box
-__device__ __forceinline__ bool grid_coord(float q, float lo, float h, int n, int &i, float &f)
+// false if q is outside the grid box.  POW2: h is a power of two, so multiplying by its inverse is the division (a
+// correctly rounded division is ten instructions, and a sample has three of these: 1920 x 1080 points on a 256^3 field,
+// whose marches are bound by the latency of one sample after another, 235 -> 218 us)
+template <bool POW2>
+__device__ __forceinline__ bool grid_coord(float q, float lo, float h, float inv_h, int n, int &i, float &f)
 {
-    const float g = rn_sub(rn_div(rn_sub(q, lo), h), 0.5f);
+    const float x = rn_sub(q, lo);
+    const float g = rn_sub(POW2 ? rn_mul(x, inv_h) : rn_div(x, h), 0.5f);
     if (g < -0.5f || g > (float)n - 0.5f) return false;
     const float gc = fminf(fmaxf(g, 0.0f), (float)(n - 1));
     i = min((int)floorf(gc), n - 2);
@@ -39,8 +45,10 @@ struct ShadowArgs {
     int np;
     float lx, ly, lz, k, eps, max_step, max_dist, jitter_scale;
     int max_steps, penumbra;
+    float inv_h;
 };
 
+template <bool POW2>
 __global__ void __launch_bounds__(256) shadow_kernel(ShadowArgs A, float *__restrict__ vis_out)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
@@ -61,8 +69,9 @@ __global__ void __launch_bounds__(256) shadow_kernel(ShadowArgs A, float *__rest
         const float qz = rn_add(pz, rn_mul(t, A.lz));
         int ix, iy, iz;
         float fx, fy, fz;
-        if (!grid_coord(qx, g.lo[0], g.h, n, ix, fx) || !grid_coord(qy, g.lo[1], g.h, n, iy, fy) ||
-            !grid_coord(qz, g.lo[2], g.h, n, iz, fz))
+        if (!grid_coord<POW2>(qx, g.lo[0], g.h, A.inv_h, n, ix, fx) ||
+            !grid_coord<POW2>(qy, g.lo[1], g.h, A.inv_h, n, iy, fy) ||
+            !grid_coord<POW2>(qz, g.lo[2], g.h, A.inv_h, n, iz, fz))
             break;
         const int64_t b = ix + (int64_t)n * (iy + (int64_t)n * iz);
         const int64_t sy = n, sz = (int64_t)n * n;
@@ -112,8 +121,14 @@ static int shadow_launch(rtsdf_grid fine, const float *fine_sdf, const float *po
     if (np == 0) return RTSDF_OK;
     const ShadowArgs A{fine,         fine_sdf, points, jitter,     np,         P.light_dir[0],
                        P.light_dir[1], P.light_dir[2], P.k, P.eps, P.max_step, P.max_dist,
-                       P.jitter_scale, P.max_steps, P.penumbra};
-    shadow_kernel<<<dim3((np + 255) / 256), dim3(256), 0, as_stream(stream)>>>(A, visibility);
+                       P.jitter_scale, P.max_steps, P.penumbra, 1.0f / fine.h};
+    const dim3 grid((np + 255) / 256), block(256);
+    int e = 0;
+    // a power of two whose inverse is a normal number too
+    if (frexpf(fine.h, &e) == 0.5f && e > -120 && e < 120)
+        shadow_kernel<true><<<grid, block, 0, as_stream(stream)>>>(A, visibility);
+    else
+        shadow_kernel<false><<<grid, block, 0, as_stream(stream)>>>(A, visibility);
     RTSDF_CHECK_LAUNCH();
     return RTSDF_OK;
 }
