@@ -11,6 +11,7 @@
 namespace rtsdf {
 
 constexpr int kWave = 64;
+constexpr int64_t kChipLds = 256 * 128 * 1024;  // bytes of LDS that blocks of 32 or 64 KB fill on 256 compute units
 // triangle references of a scene (after splitting) at most: record offsets (48 B each) are formed with the
 // full-rate 24-bit multiply
 constexpr int kMaxRefs = 1 << 24;

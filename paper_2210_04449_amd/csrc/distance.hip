@@ -87,18 +87,26 @@ __device__ __forceinline__ float box_dist2(float px, float py, float pz, float x
     return dx * dx + dy * dy + dz * dz;
 }
 
-constexpr int kDistBlock = 128;
+// Bound by latency (dependent node loads) at the occupancy that the stacks leave, 8 bytes per entry and lane, and by
+// the points on the medial axis, which see a thousand triangles at one distance.  A block is one wavefront, so that
+// a slow one holds no other's LDS.  SHORT: the first of two launches, with 20 stack entries instead of the 32 or 64 of
+// the deepest hierarchy, so 15 wavefronts per compute unit instead of 9 or 4; a point that would push past them leaves
+// kPointTodo as its distance, and the second launch, with the full stack, takes those points only.  2,000,003 texels
+// against 223,228 triangles: 1,834 -> 1,244 us (16 entries: 1,374, with too many points left over; 24: 1,487).
+constexpr int kDistBlock = 64;
+constexpr uint32_t kPointTodo = 0x7FA5A5A5u;  // a NaN that no distance is
+constexpr int kShortDistStack = 20;
 
-template <int SD, bool TEXELS>
-__global__ void __launch_bounds__(kDistBlock) point_distance_kernel(BvhView S, int nt, const float *__restrict__ pts,
-                                                                    rtsdf_grid g, const int32_t *__restrict__ texels,
-                                                                    int n, float *__restrict__ dist_out,
-                                                                    int32_t *__restrict__ tri_out)
+template <int SD, bool TEXELS, bool SHORT>
+__global__ void __launch_bounds__(kDistBlock)
+point_distance_kernel(BvhView S, int nt, const float *__restrict__ pts, rtsdf_grid g,
+                      const int32_t *__restrict__ texels, int n, float *dist_out, int32_t *__restrict__ tri_out,
+                      bool todo_only)
 {
     __shared__ int stk_node[kDistBlock / kWave][SD][kWave];
     __shared__ float stk_d2[kDistBlock / kWave][SD][kWave];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || (todo_only && __float_as_uint(dist_out[i]) != kPointTodo)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float px, py, pz;
     if (TEXELS) {
@@ -114,6 +122,30 @@ __global__ void __launch_bounds__(kDistBlock) point_distance_kernel(BvhView S, i
     int best_id = -1;
     int sp = 0;
     int node = nt > 0 ? 0 : kDone;
+    if (SHORT && nt > 0) {
+        // a first bound, so that few boxes wait on the stack: the leaf next to one of the points, reached by all of
+        // them through scalar loads
+        const float cx = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(px)));
+        const float cy = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(py)));
+        const float cz = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(pz)));
+        int at = 0;
+        while (at >= 0) {
+            const sfloat *nd = node_sptr(S.nodes, at);
+            const float e0 = box_dist2(cx, cy, cz, nd[0], nd[1], nd[2], nd[3], nd[8], nd[9]);
+            const float e1 = box_dist2(cx, cy, cz, nd[4], nd[5], nd[6], nd[7], nd[10], nd[11]);
+            at = __builtin_amdgcn_readfirstlane(__float_as_int(e1 < e0 ? nd[13] : nd[12]));
+        }
+        for (int k = leaf_first(at); k < leaf_first(at) + leaf_count(at); ++k) {
+            const float4 *tp = tri_ptr(S.tris, k);
+            const float4 A = tp[0];
+            const float d2 = point_tri_dist2(px, py, pz, A, tp[1], tp[2]);
+            const int id = __float_as_int(A.w);
+            if (d2 < best || (d2 == best && id < best_id)) {
+                best = d2;
+                best_id = id;
+            }
+        }
+    }
     while (node != kDone) {
         if (node >= 0) {
             const BvhNode *nd = node_ptr(S.nodes, node);
@@ -124,6 +156,10 @@ __global__ void __launch_bounds__(kDistBlock) point_distance_kernel(BvhView S, i
             const bool h0 = e0 <= best, h1 = e1 <= best;  // ties kept: a tie in distance may hold a lower id
             const bool first0 = h0 && (!h1 || e0 <= e1);
             if (h0 && h1) {
+                if (SHORT && sp == SD) {
+                    dist_out[i] = __uint_as_float(kPointTodo);
+                    return;
+                }
                 stk_node[wave][sp][lane] = first0 ? m.y : m.x;
                 stk_d2[wave][sp][lane] = first0 ? e1 : e0;
                 ++sp;
@@ -170,16 +206,24 @@ static int point_distance_launch(const rtsdf_scene *scene, const float *points, 
     const BvhView S{scene->nodes, scene->tris, scene->tmap};
     const dim3 grid((unsigned)((n + kDistBlock - 1) / kDistBlock)), block(kDistBlock);
     hipStream_t s = as_stream(stream);
+    const int full = sd <= 32 ? 32 : 64;
+    // the short stack pays from about three fills of the chip on: below, a launch lasts as long as its slowest points,
+    // which go through both launches (400,000 points, 223,228 triangles: 1,234 -> 1,145 us; 250,000: 1,036 -> 1,130)
+    const bool two = (int64_t)n * full * 8 > 3 * kChipLds && sd > kShortDistStack;
+    const auto launch = [&](auto kernel, bool todo_only) {
+        kernel<<<grid, block, 0, s>>>(S, scene->nt, points, g, texels, n, dist, tri, todo_only);
+    };
+    if (two) {
+        if (texel_mode) launch(point_distance_kernel<kShortDistStack, true, true>, false);
+        else launch(point_distance_kernel<kShortDistStack, false, true>, false);
+        RTSDF_CHECK_LAUNCH();
+    }
     if (texel_mode) {
-        if (sd <= 32)
-            point_distance_kernel<32, true><<<grid, block, 0, s>>>(S, scene->nt, nullptr, g, texels, n, dist, tri);
-        else
-            point_distance_kernel<64, true><<<grid, block, 0, s>>>(S, scene->nt, nullptr, g, texels, n, dist, tri);
+        if (full == 32) launch(point_distance_kernel<32, true, false>, two);
+        else launch(point_distance_kernel<64, true, false>, two);
     } else {
-        if (sd <= 32)
-            point_distance_kernel<32, false><<<grid, block, 0, s>>>(S, scene->nt, points, g, nullptr, n, dist, tri);
-        else
-            point_distance_kernel<64, false><<<grid, block, 0, s>>>(S, scene->nt, points, g, nullptr, n, dist, tri);
+        if (full == 32) launch(point_distance_kernel<32, false, false>, two);
+        else launch(point_distance_kernel<64, false, false>, two);
     }
     RTSDF_CHECK_LAUNCH();
     return RTSDF_OK;
