@@ -441,6 +441,23 @@ __device__ __forceinline__ int stack_pop(int stride, int &sp, const lds_int *stk
     return v;
 }
 
+// The same stack by the address of its next entry (queued loop): the address is the register itself, and as a lane's
+// entries are kWave words apart in its wavefront's part, the bounds are compares with wave-uniform addresses.
+__device__ __forceinline__ void stack_push_at(int stride, lds_int *&top, lds_int *end, int32_t *spill, int v)
+{
+    if (top < end) *top = v;
+    else spill[__umul24((uint32_t)(top - end) / kWave, (uint32_t)stride)] = v;
+    top += kWave;
+}
+
+// (of a stack that is not empty)
+__device__ __forceinline__ int stack_pop_at(int stride, lds_int *&top, lds_int *end, const int32_t *spill)
+{
+    top -= kWave;
+    if (top < end) return *top;
+    return spill[__umul24((uint32_t)(top - end) / kWave, (uint32_t)stride)];
+}
+
 // One internal node: test both children's boxes, descend into the nearer hit
 // child and push the farther one; pop when neither is hit.
 template <int SL, bool STATS>
@@ -593,6 +610,42 @@ __device__ __forceinline__ void node_step_regs(const RaySetup &R, float4 a, floa
     // (bitwise, so the compiler keeps it branch-free)
     const bool second = h1 & ((t1 < t0) | ((t1 == t0) & (e1 < e0)));
     node_decide(h0, h1, h0 & !second, m, node, tri_cur, tri_end, push, push_val, pop);
+}
+
+// Queued loop: a lane's pending triangles as one word, their number above the first one's leaf-order index, so that a
+// leaf child is unpacked by a rotation and "one pending", "two pending" are compares of the word itself.
+constexpr uint32_t kPendOne = 1u << 27;
+static_assert(kMaxRefs <= 1 << 26, "an index shifted by the queue entries' six lane bits loses only the number");
+__device__ __forceinline__ uint32_t leaf_pending(int code)
+{
+    return __builtin_amdgcn_alignbit(~(uint32_t)code, ~(uint32_t)code, 5);
+}
+
+// node_step's decisions for the queued loop.  The best distance is compared, not folded into the exits (its bits come
+// from LDS: a minimum would first have to quiet it), and of two equal entries the first child is taken: rays start at
+// their entry points, few of which contain them.
+__device__ __forceinline__ void node_step_queued(const RaySetup &R, float4 a, float4 b, float4 z, int2 m, int &node,
+                                                 float tbest, uint32_t &pend, bool &push, int &push_val, bool &pop)
+{
+    const auto slab = [&](float lx, float hx, float ly, float hy, float lz, float hz, float &t) {
+        const float x0 = fmaf(lx, R.ix, -R.oix), x1 = fmaf(hx, R.ix, -R.oix);
+        const float y0 = fmaf(ly, R.iy, -R.oiy), y1 = fmaf(hy, R.iy, -R.oiy);
+        const float z0 = fmaf(lz, R.iz, -R.oiz), z1 = fmaf(hz, R.iz, -R.oiz);
+        t = fmaxf(fmaxf(fminf(x0, x1), fminf(y0, y1)), fmaxf(fminf(z0, z1), 0.0f));
+        return t <= fminf(fminf(fmaxf(x0, x1), fmaxf(y0, y1)), fmaxf(z0, z1)) && t <= tbest;
+    };
+    float t0, t1;
+    const bool h0 = slab(a.x, a.y, a.z, a.w, z.x, z.y, t0);
+    const bool h1 = slab(b.x, b.y, b.z, b.w, z.z, z.w, t1);
+    const bool any = h0 || h1, both = h0 && h1;
+    const bool first0 = h0 && !(h1 && t1 < t0);
+    const int near = first0 ? m.x : m.y, far = first0 ? m.y : m.x;
+    const bool near_leaf = any && near < 0;
+    pend = near_leaf ? leaf_pending(near) : 0u;
+    push = both && !near_leaf;
+    push_val = far;
+    pop = !any || (near_leaf && !both);
+    node = near_leaf ? far : near;
 }
 
 __device__ __forceinline__ void node_step_flat(const BvhView &S, const RaySetup &R, int &node, float tbest,
@@ -1076,6 +1129,15 @@ trace_persistent(TraceArgs A)
         return __builtin_amdgcn_readfirstlane(lo);
     };
 
+    // A scene's record for one round of the loop below, read anew by scalar loads: kept over the traversal, its fields
+    // would be spilled to vector registers' lanes, an instruction for each word on every way.
+    const auto record = [&](int sn) {
+        scene_ptr p = BATCHED ? (scene_ptr)(uintptr_t)uniform64((uint64_t)(uintptr_t)(A.scenes + sn))
+                              : (scene_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return p;
+    };
+
     // wave-uniform context state: -1 free, else rays not yet finished | texels << 16; and the scene (batches)
     int cstate[2] = {-1, -1}, cscene[2] = {0, 0};
     int cur = 0, pool = 0, nrays = 0;  // the context rays are handed out from
@@ -1088,6 +1150,9 @@ trace_persistent(TraceArgs A)
     float tbest = __builtin_inff();
     int ibest = -1, node = kDone, leaf = kDone, sp = 0;
     int tri_cur = 0, tri_end = 0;
+    // queued loop: the pending triangles, the stack's next entry and the end of the wavefront's part of it in LDS
+    uint32_t pend = 0;
+    lds_int *top = stk, *const stk_end = (lds_int *)(stack_mem + (wave + 1) * SL * kWave);
     bool front = false;
     EntryCursor E{0u, 0u, nullptr};  // queued loop: the entry points not yet visited (bit kEntryEnd: none left)
 
@@ -1131,10 +1196,11 @@ trace_persistent(TraceArgs A)
         }
 
         // ---- refill idle lanes from the current tile, in bin order
-        const TraceScene &P = BATCHED ? A.scenes[cscene[cur]] : A.one;
+        const scene_ptr Pp = record(cscene[cur]);
+        const auto &P = *Pp;
         const int R = P.rays;
         const int nfm = P.nf - 1;
-        const BvhView S = P.bvh;
+        const BvhView S{P.bvh.nodes, P.bvh.tris, P.bvh.tmap};
         const int scene_nt = P.nt;
         {
             const uint64_t need = __builtin_amdgcn_ballot_w64(!busy);
@@ -1172,6 +1238,7 @@ trace_persistent(TraceArgs A)
                     leaf = kDone;
                     tri_cur = tri_end = 0;
                     sp = 0;
+                    top = stk;
                     busy = true;
                 }
                 pool += take;
@@ -1304,13 +1371,19 @@ trace_persistent(TraceArgs A)
                 // in LDS (two per iteration at most) and goes on with its traversal; once a wavefront's
                 // worth of tests is queued, every lane takes one, whichever ray it belongs to, so the
                 // triangle code runs at full width instead of in nearly every iteration for a few lanes.
+                // The loop is bound by vector instructions and, nearly as much, by the data return of its loads: an
+                // iteration is 90 instructions and 56 bytes a lane (106 and 64 before the pending word, the queue
+                // without wrap-around, the stack by address and the shorter node step; with the scenes' records read
+                // anew each round, 28 registers' worth of spilled scalars less per round).  Room, 216k triangles,
+                // 128^3 / 256^3, 16 rays: 20.1 -> 19.5 ms; 12 scenes in one launch: 17.8 -> 17.1 ms.
                 // Between flushes a lane culls boxes against its ray's best distance as of the last flush
                 // (a larger bound only enters more boxes); the closest hit is the minimum of the
                 // (t, triangle id, facing) keys of all tests, as in the other loops.
-                int qh = 0, qt = 0;  // wave-uniform head and tail (entries at index & (kQueueCap - 1))
+                int qn = 0;  // tests queued (wave-uniform)
                 const auto flush = [&](int nf) {
                     const bool act = lane < nf;
-                    const uint32_t e = act ? T.q[(qh + lane) & (kQueueCap - 1)] : (uint32_t)lane;
+                    const uint32_t e = act ? T.q[lane] : (uint32_t)lane;
+                    if (qn > kWave) T.q[lane] = T.q[kWave + lane];  // the later ones move up
                     const int owner = (int)(e & 63u), addr = owner << 2;
                     // the owner's ray, from its registers (every lane takes part in the permutes)
                     const float ox = __int_as_float(__builtin_amdgcn_ds_bpermute(addr, __float_as_int(Rs.ox)));
@@ -1332,66 +1405,78 @@ trace_persistent(TraceArgs A)
                             atomicMin(&T.best[owner], key);
                         }
                     }
-                    qh += nf;
+                    qn -= nf;
                     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                     __builtin_amdgcn_wave_barrier();
                     tbest = __uint_as_float((uint32_t)(T.best[lane] >> 32));
                 };
+                // (lanes without a ray hold kDone and no pending triangles)
                 while (true) {
                     if (STATS) {
                         ++st_iters;
-                        st_busy += busy && (node != kDone || tri_cur < tri_end);
+                        st_busy += node != kDone || pend >= kPendOne;
                     }
                     // ---- append up to two of the lane's pending triangles, as far as the queue has room
-                    // (lanes without a ray hold an empty range)
-                    const int c = min(tri_end - tri_cur, 2);
-                    const uint64_t b1 = __builtin_amdgcn_ballot_w64(c >= 1), b2 = __builtin_amdgcn_ballot_w64(c >= 2);
+                    bool g1 = pend >= kPendOne, g2 = pend >= 2 * kPendOne;
+                    const uint64_t b1 = __builtin_amdgcn_ballot_w64(g1), b2 = __builtin_amdgcn_ballot_w64(g2);
                     // the lane's position: the requests of the lanes below it
                     const int pos = (int)__builtin_amdgcn_mbcnt_hi(
                         (uint32_t)(b2 >> 32),
                         __builtin_amdgcn_mbcnt_lo(
                             (uint32_t)b2, __builtin_amdgcn_mbcnt_hi((uint32_t)(b1 >> 32),
                                                                     __builtin_amdgcn_mbcnt_lo((uint32_t)b1, 0u))));
-                    int total = (int)(__popcll(b1) + __popcll(b2)), g = c;
-                    if (qt - qh + total > kQueueCap) {  // rare: grant a prefix of the lanes
-                        g = pos + c <= kQueueCap - (qt - qh) ? c : 0;
-                        total = (int)(__popcll(__builtin_amdgcn_ballot_w64(g >= 1)) + __popcll(__builtin_amdgcn_ballot_w64(g >= 2)));
+                    int total = (int)(__popcll(b1) + __popcll(b2));
+                    if (qn + total > kQueueCap) {  // rare: grant a prefix of the lanes
+                        const bool fit = pos + (g2 ? 2 : 1) <= kQueueCap - qn;
+                        g1 = g1 && fit;
+                        g2 = g2 && fit;
+                        total = (int)(__popcll(__builtin_amdgcn_ballot_w64(g1)) +
+                                      __popcll(__builtin_amdgcn_ballot_w64(g2)));
                     }
-                    if (g > 0) {
-                        const uint32_t e = ((uint32_t)tri_cur << 6) | (uint32_t)lane;
-                        T.q[(qt + pos) & (kQueueCap - 1)] = e;
-                        if (g > 1) T.q[(qt + pos + 1) & (kQueueCap - 1)] = e + 64u;
-                        tri_cur += g;
+                    if (g1) {
+                        uint32_t *q = T.q + qn + pos;
+                        const uint32_t e = (pend << 6) | (uint32_t)lane;
+                        q[0] = e;
+                        pend -= kPendOne - 1u;
+                        if (g2) {
+                            q[1] = e + 64u;
+                            pend -= kPendOne - 1u;
+                        }
                     }
-                    qt += total;
+                    qn += total;
                     // ---- the lane's traversal step: a node, or opening a popped leaf
-                    const bool idle = busy && tri_cur >= tri_end;
+                    const bool idle = pend < kPendOne;
                     const bool do_node = idle && node >= 0;
                     const float4 *q = reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(S.nodes) +
                                                                        (uint32_t)(do_node ? node : 0) * 64u);
                     const float4 w0 = q[0], w1 = q[1], w2 = q[2];
-                    const int2 w3 = *reinterpret_cast<const int2 *>(q + 3);
+                    const v2i w3 = *reinterpret_cast<const v2i *>(q + 3);
                     bool push = false, pop = false;
                     int push_val = 0;
                     if (do_node) {
                         if (STATS) ++st_nodes;
-                        const int4 m = make_int4(w3.x, w3.y, 0, 0);
-                        node_step_regs(Rs, w0, w1, w2, m, node, tbest, tri_cur, tri_end, push, push_val, pop);
-                        if (STATS) st_empty += pop && tri_cur >= tri_end;
+                        node_step_queued(Rs, w0, w1, w2, make_int2(w3.x, w3.y), node, tbest, pend, push, push_val, pop);
+                        if (STATS) st_empty += pop && pend < kPendOne;
                     } else if (idle && node != kDone) {
-                        tri_cur = leaf_first(node);
-                        tri_end = tri_cur + leaf_count(node);
+                        pend = leaf_pending(node);
                         pop = true;
                     }
-                    if (push) stack_push<SL>(stride, sp, stk, spill, push_val);
-                    if (pop) node = sp || !ENTRIES ? stack_pop<SL>(stride, sp, stk, spill) : entry_pop(E, tbest);
+                    if (push) stack_push_at(stride, top, stk_end, spill, push_val);
+                    if (pop) {
+                        // (formed anew in each iteration: a scalar register less to keep and to spill)
+                        int room = SL - 1;
+                        asm volatile("" : "+s"(room));
+                        if (top >= stk_end - room * kWave) node = stack_pop_at(stride, top, stk_end, spill);
+                        else node = ENTRIES ? entry_pop(E, tbest) : kDone;
+                    }
                     // ---- a wavefront's worth of tests
-                    if (qt - qh >= kWave) flush(kWave);
-                    const uint64_t done = wave_done(busy, node, tri_cur, tri_end);
+                    if (qn >= kWave) flush(kWave);
+                    const uint64_t done = __builtin_amdgcn_ballot_w64(node == kDone) &
+                                          __builtin_amdgcn_ballot_w64(pend < kPendOne);
                     if (__popcll(done) >= refill_at) break;
                 }
                 // the rest of the queue (the finished rays' tests among them)
-                while (qt - qh > 0) flush(min(qt - qh, kWave));
+                while (qn > 0) flush(min(qn, kWave));
             } else if (LOOP == 2) {
                 while (true) {
                     if (STATS) {
@@ -1443,7 +1528,7 @@ trace_persistent(TraceArgs A)
                     if (__popcll(done) >= refill_at) break;
                 }
             }
-            const bool fin = busy && node == kDone && leaf == kDone && tri_cur >= tri_end;
+            const bool fin = busy && node == kDone && (QUEUED ? pend < kPendOne : leaf == kDone && tri_cur >= tri_end);
             if (fin) {
                 if (STATS) ++st_rays;
                 int id = -1;
@@ -1479,7 +1564,8 @@ trace_persistent(TraceArgs A)
             if (cstate[c] < 0 || (cstate[c] & 0xFFFF) > 0) continue;
             const int nt = cstate[c] >> 16, e = c * kTileTexels + lane;
             cstate[c] = -1;
-            const TraceScene &Q = BATCHED ? A.scenes[cscene[c]] : A.one;
+            const scene_ptr Qp = record(cscene[c]);
+            const auto &Q = *Qp;
             if (lane < nt && T.tex[e] >= 0) {
                 const int j = T.tex[e];
                 const unsigned long long key = T.key[e];
