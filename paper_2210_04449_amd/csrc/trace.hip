@@ -678,7 +678,7 @@ constexpr int kQueueCap = 128;
 constexpr unsigned long long kBestInit = 0x7F800000FFFFFFFFull;  // t = +inf, no triangle
 constexpr int kMaxQueuedRefs = 1 << 26;  // queue entries: leaf-order index << 6 | lane
 static_assert(2 * kWave <= kQueueCap && (kQueueCap & (kQueueCap - 1)) == 0, "queue size");
-static_assert(kBins <= kQueueCap, "the bin counters share the queue's words");
+static_assert(kBins + kWave <= kQueueCap, "the bin counters share the queue's words");
 
 // Entry points of a tile at most: the bits of two mask words, the last of which marks the end.  At 31, 46 and 62 the
 // room (216k triangles, 128^3 / 256^3, 16 rays) traces in 22.4, 21.5 and 21.1 ms and visits 17.9, 15.3 and 13.1 nodes a
@@ -1138,7 +1138,9 @@ trace_persistent(TraceArgs A)
         return p;
     };
 
-    // wave-uniform context state: -1 free, else rays not yet finished | texels << 16; and the scene (batches)
+    // wave-uniform context state: -1 free, else rays not yet finished | texels << 16; and the scene (batches).  Two of
+    // them in two-level scenes too, where a ray keeps its world direction in LDS: a room of 120 objects with rigid parts,
+    // 256^3, 5 rays: 8,980 -> 8,300 us (lanes with work 0.69 -> 0.79 of lane-iterations)
     int cstate[2] = {-1, -1}, cscene[2] = {0, 0};
     int cur = 0, pool = 0, nrays = 0;  // the context rays are handed out from
     uint32_t rdiv = 0;                 // its q / R multiplier (below)
@@ -1167,7 +1169,7 @@ trace_persistent(TraceArgs A)
                 gnext = g < all_tiles ? g : -1;
             }
             const int sn = gnext >= 0 && BATCHED ? scene_of(gnext) : 0;
-            if (gnext >= 0 && (!any_busy || (!INST && (!BATCHED || sn == cscene[cur])))) {
+            if (gnext >= 0 && (!any_busy || !BATCHED || sn == cscene[cur])) {
                 const int c = cur ^ 1, g = gnext;
                 gnext = -2;
                 const TraceScene &P = BATCHED ? A.scenes[sn] : A.one;
@@ -1235,6 +1237,11 @@ trace_persistent(TraceArgs A)
                     ibest = -1;
                     front = false;
                     if (QUEUED) T.best[lane] = kBestInit;
+                    if (INST) {  // the world direction, for the way back from a part (in words of the queued loop's:
+                        // the tile's own direction buffer is the next tile's by then)
+                        T.best[lane] = (unsigned long long)__float_as_uint(d.y) << 32 | __float_as_uint(d.x);
+                        T.q[kBins + lane] = __float_as_uint(d.z);
+                    }
                     leaf = kDone;
                     tri_cur = tri_end = 0;
                     sp = 0;
@@ -1252,7 +1259,7 @@ trace_persistent(TraceArgs A)
         {
             // refill rounds go on while this tile has rays or the next one can start before every lane is
             // done; otherwise every lane finishes first
-            const bool early = !INST && cstate[cur ^ 1] < 0 &&
+            const bool early = cstate[cur ^ 1] < 0 &&
                                (gnext == -2 || (gnext >= 0 && (!BATCHED || scene_of(gnext) == cscene[cur])));
             const int refill_at = __builtin_amdgcn_readfirstlane(pool < nrays || early ? REFILL : kWave);
             if (STATS) st_drains += refill_at == kWave && gnext != -1;  // every lane finishes before the next tile
@@ -1347,9 +1354,10 @@ trace_persistent(TraceArgs A)
                     } else if (INST && busy && node == kReturn) {
                         // the part is done (its last leaf's triangles too): the world ray again, as drawn
                         const int j = T.tex[rid >> 6];
-                        const float4 d = dirs[((rid >> 6) & (kTileTexels - 1)) * R + (rid & 63)];
+                        const unsigned long long dxy = T.best[lane];
                         ray_setup(texel_coord(P.lox, j & nfm, P.hf), texel_coord(P.loy, (j >> P.lognf) & nfm, P.hf),
-                                  texel_coord(P.loz, j >> (2 * P.lognf), P.hf), d.x, d.y, d.z, Rs);
+                                  texel_coord(P.loz, j >> (2 * P.lognf), P.hf), __uint_as_float((uint32_t)dxy),
+                                  __uint_as_float((uint32_t)(dxy >> 32)), __uint_as_float(T.q[kBins + lane]), Rs);
                         pop = true;
                     } else if (busy && node != kDone) {
                         tri_cur = leaf_first(node);

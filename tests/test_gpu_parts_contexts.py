@@ -1,0 +1,44 @@
+"""Two-level scenes with two tile contexts per wavefront: rays of a tile that are still inside a part when the next tile's
+directions are drawn come back with their own direction, so a launch over many tiles gives, bit for bit, what launches
+over too few tiles for a second context give."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("rays,tile", [(1, 64), (5, 16), (16, 32), (48, 16)])
+def test_parts_many_tiles_like_few(rays, tile):
+    import torch
+    import paper_2210_04449_amd.rtsdf as R
+    from paper_2210_04449_amd.pipeline import Pipeline
+    from synth.scenes import rigid_parts
+    v, f, offs, T = rigid_parts()
+    nc, nf = 64, 128
+
+    def cu(a):
+        return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    out = []
+    for chunk in (None, 2048):
+        p = Pipeline(cu(v), cu(f), nc, nf, 0.5 / nc, 3.0 / nc, rays, seed=5, scene_id=3, alpha=0.9, parts=(offs, cu(T)))
+        p.scene.set_tuning(tile_texels=tile, stats=1)
+        p.voxelize()
+        p.jfa()
+        p.select()
+        torch.cuda.synchronize()
+        n = int(p.count.item())
+        early = 0
+        for frame in range(2):
+            for a in range(0, n, chunk or n):
+                queue = p.queue[a:min(n, a + (chunk or n))].contiguous()
+                count = torch.full((1,), queue.numel(), dtype=torch.int32, device="cuda")
+                R.rtsdf_trace_accumulate(p.scene, p.coarse, p.coarse_sdf, p.fine, p.mask, queue, count, p.rays, frame,
+                                         p.seed, p.scene_id, p.alpha, p.state, p.fine_sdf, p.trace_ws)
+                torch.cuda.synchronize()
+                early += int(p.trace_ws[72:80].view(torch.int64).item()) // 64
+        assert (early > 0) == (chunk is None), early
+        out.append({k: t.cpu().numpy() for k, t in {**p.state.tensors(), "fine": p.fine_sdf}.items()})
+        p.close()
+    assert n > 100000
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k], equal_nan=True), k
