@@ -458,7 +458,7 @@ __global__ void __launch_bounds__(256) coarse_trilinear_quads(const float *__res
         // left of the first coarse centre the cell is that of columns 0 and 1 (weight 0)
         const int lo = LOGR == 1 ? (q + 1) / 2 : LOGR == 2 ? q / 2 : 0;
         const bool first = LOGR <= 2 && k == 0 && (LOGR == 1 ? q == 0 : q < 2);
-        float xl[4], m = -__builtin_inff();
+        float xl[4], m = __builtin_nanf("");  // the largest corner that is a number, as above: NaN if there is none
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
             const float a = first ? col[w][1] : col[w][lo], b = first ? col[w][NC > 2 ? 2 : 1] : col[w][lo + 1];
