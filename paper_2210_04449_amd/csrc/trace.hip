@@ -196,7 +196,9 @@ __device__ __noinline__ float tri_watertight(float ox, float oy, float oz, float
     if (det == 0.0f) return 0.0f;
     const float T = U * (Sz * va[kz]) + V * (Sz * vb[kz]) + W * (Sz * vc[kz]);
     const float t = T / det;
-    if (!(t > 0.0f)) return 0.0f;
+    // T is past the largest float where large triangles are far: a t of +inf would equal the bound of a ray that has met
+    // nothing yet, which has no triangle whose id could be compared
+    if (!(t > 0.0f && t <= 3.0e38f)) return 0.0f;
     return det > 0.0f ? t : -t;
 }
 
