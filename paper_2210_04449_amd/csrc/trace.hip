@@ -969,7 +969,8 @@ __device__ __noinline__ void tile_setup(scene_ptr P_, lds_tile<ENTRIES> *T_, gv4
             rank += ok < eord || (ok == eord && k < lane);
         }
         if (lane < nentry) {
-            const float least = 0.9999f * __builtin_amdgcn_sqrtf(ed2) - slack;
+            // (past the largest float the order is not known: such an entry point ends no ray)
+            const float least = ed2 < __builtin_inff() ? 0.9999f * __builtin_amdgcn_sqrtf(ed2) - slack : 0.0f;
             entry[rank] = v2i{ecode, __float_as_int(least)};
             T->q[rank] = (uint32_t)eref;
         }
