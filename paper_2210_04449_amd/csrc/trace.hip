@@ -377,7 +377,7 @@ struct TraceArgs {
     int spill_stride;            // lanes in the launch
     int bin_directions;          // sort each tile's rays by direction bin
     int tile_cap;                // texels per wavefront tile at most (16, 32 or 64)
-    int few_rays;                // queued loop without entry points (see kFewRays)
+    int few_rays;                // single scene: queued loop without entry points (see kFewRays)
     float4 *dirs;                // per wavefront: kTileRays directions, then kTileRays records in bin order
 };
 
@@ -694,10 +694,15 @@ constexpr int kEntryStack = 4;  // stack entries per lane whose LDS the two cont
 // round's largest such value, so that the nodes that matter most are open when the 62 run out (0.25: 2 % slower; one
 // node at a time, 61 rounds instead of about 25: 4 % slower; all above kOpen: 20 % slower).
 constexpr float kOpen = 4.0f, kOpenTogether = 0.5f;
-// Tiles of at most this many rays start at the root (loop shape 5, chosen at launch): choosing entry points, and
-// their place in the traversal loop, cost more than the node visits they save.  With entry points, 64 texels x 1 ray
-// trace 2 to 4 % slower (room-like scene, 128^3 / 256^3: 2,206 against 2,284 us an update), x 2 rays 1.5 % slower, x 3
-// rays 9 % faster (4,243 against 3,864 us).
+// A single scene whose tiles can have at most this many rays, by their number per texel and the tile_texels of the
+// tuning (1 or 2 rays with the default 64), starts its rays at the root: loop shape 5, chosen at launch.  Choosing entry
+// points, and their place in the traversal loop, cost more than the node visits they save.  With entry points, 64 texels
+// x 1 ray trace 2 to 4 % slower (room-like scene, 128^3 / 256^3: 2,206 against 2,284 us an update), x 2 rays 1.5 %
+// slower, x 3 rays 9 % faster (4,243 against 3,864 us).  The line is not that of the tile a launch ends up with: small
+// launches of more rays, whose tiles tile_texels_auto cuts down to 128 rays, are as fast or faster with entry points
+// (traces of 4 rays: 322 triangles at 32^3 / 64^3 143 against 142 us, a room at 32^3 251 against 257, at 64^3 779
+// against 854).  Batches always choose them: of 12 rooms at 64^3 1 ray is 5 % slower (4,410 against 4,189 us a step),
+// 2 rays are even (6,200 against 6,190), and of 6 at 128^3 2 rays are 2 % faster (20,365 against 20,684).
 constexpr int kFewRays = 128;
 
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -1822,8 +1827,9 @@ static int launch_trace3(const TraceArgs &A, const rtsdf_trace_tuning &T, hipStr
     case 1: return launch_trace4<SL, REFILL, 1, BATCHED>(A, T, s);
     case 2: return launch_trace4<SL, REFILL, 2, BATCHED>(A, T, s);
     case 4:
-        return A.few_rays ? launch_trace4<SL, REFILL, 5, BATCHED>(A, T, s)
-                          : launch_trace4<SL, REFILL, 4, BATCHED>(A, T, s);
+        if constexpr (!BATCHED)  // (see kFewRays)
+            if (A.few_rays) return launch_trace4<SL, REFILL, 5, false>(A, T, s);
+        return launch_trace4<SL, REFILL, 4, BATCHED>(A, T, s);
     default: return launch_trace4<SL, REFILL, 3, BATCHED>(A, T, s);
     }
 }
