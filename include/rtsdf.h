@@ -474,9 +474,11 @@ int rtsdf_trace_accumulate(const rtsdf_scene *scene, rtsdf_grid coarse, const fl
  *                   lane takes one (of any lane's ray); traversals cull
  *                   with their ray's best distance as of the last queue
  *                   flush, and start at the subtrees that rays from their
- *                   tile can meet instead of at the root.  Two-level scenes, 4-wide traversals and scenes
- *                   of 2^26 or more triangle references use 3 instead;
- *                   default 4;
+ *                   tile can meet instead of at the root (single scenes whose
+ *                   tiles hold at most 128 rays by tile_texels and the ray
+ *                   count start at the root).  Two-level scenes, 4-wide
+ *                   traversals and scenes of 2^26 or more triangle references
+ *                   use 3 instead; default 4;
  *   bin_directions  1: each wavefront's tile of rays is sorted by direction
  *                   before tracing (coherence); 0: queue order;
  *   stack_lds       traversal stack entries kept in LDS per lane (12, 16 or
@@ -484,7 +486,9 @@ int rtsdf_trace_accumulate(const rtsdf_scene *scene, rtsdf_grid coarse, const fl
  *                   entry points take); deeper entries go to the workspace's
  *                   spill area;
  *   tile_texels     texels per wavefront tile at most (16, 32 or 64; a tile
- *                   also holds at most 768 rays, i.e. 768 / rays texels);
+ *                   also holds at most 768 rays, i.e. 768 / rays texels, and
+ *                   a launch of few rays on a single scene takes smaller
+ *                   tiles so that all wavefronts get some);
  *   bvh_width       2: traverse the two-child hierarchy; 4: a 4-wide copy of
  *                   it (each wide node takes up to four descendants of a
  *                   two-child node, greedily by box area; the boxes are the

@@ -76,7 +76,8 @@ struct FillScene {
 
 __global__ void __launch_bounds__(256) voxelize_batch(const BatchVox *__restrict__ sc, int ns, int64_t items)
 {
-    // the same strided dealing of items to wavefronts as the single-scene kernel
+    // a lane per (triangle, axis), dealt to wavefronts with a stride, so that the large projections of consecutive
+    // triangles land in different wavefronts
     const int64_t waves = (items + kWave - 1) / kWave;
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t item = (gid & (kWave - 1)) * waves + (gid >> 6);

@@ -92,7 +92,10 @@ __device__ __forceinline__ float box_dist2(float px, float py, float pz, float x
 // a slow one holds no other's LDS.  SHORT: the first of two launches, with 20 stack entries instead of the 32 or 64 of
 // the deepest hierarchy, so 15 wavefronts per compute unit instead of 9 or 4; a point that would push past them leaves
 // kPointTodo as its distance, and the second launch, with the full stack, takes those points only.  2,000,003 texels
-// against 223,228 triangles: 1,834 -> 1,244 us (16 entries: 1,374, with too many points left over; 24: 1,487).
+// in three rooms of 300 objects (about 210,000 triangles; how many points lie on the medial axis differs between them):
+// two wavefronts a block and the full stack 1,713 / 1,748 / 1,980 us, one 1,421 / 1,440 / 1,690, 16 entries first
+// 1,224 / 1,236 / 1,674 (more points left over), 20 entries first 1,090 / 1,127 / 1,488.  These hierarchies are at most
+// 24 deep, so that with 24 entries the full stack goes alone.
 constexpr int kDistBlock = 64;
 constexpr uint32_t kPointTodo = 0x7FA5A5A5u;  // a NaN that no distance is
 constexpr int kShortDistStack = 20;

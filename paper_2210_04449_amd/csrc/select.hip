@@ -16,7 +16,8 @@
 //                  through LDS, block offset from the scan; writes r^3 queue
 //                  entries per selected voxel
 //   select_mask    the linear uint8 mask, four texels per lane
-// Grids of 64^3 cells and more take wider kernels of the same steps:
+// Batches run these over all their scenes.  Single grids of 64^3 cells and more
+// take wider kernels of the same steps:
 //   select_rows    counts and mask in one read of the predicate, four cells
 //                  (16 bytes) per lane in rows of 64
 //   select_scan, or select_chunks + select_chunk_scan above 4096 blocks

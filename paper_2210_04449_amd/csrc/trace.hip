@@ -1074,10 +1074,9 @@ __global__ void trace_tile_prefix(const TraceScene *scenes, int n, int cap, int3
 // ray, it sorts the next tile's rays into the other context and refills its
 // lanes from there while the first tile's last rays are still traced (a
 // tile's Eq. (1) epilogue runs once its last ray is done), so lanes do not
-// wait for the slowest ray of each tile.  Two-level scenes, and a next tile
-// of another scene in a batch, start only once every lane is done (a part's
-// exit re-reads its ray's direction by ray id; the traversal takes the
-// scene's hierarchy as a wave-uniform value).
+// wait for the slowest ray of each tile.  A next tile of another scene in a
+// batch starts only once every lane is done (the traversal takes the scene's
+// hierarchy as a wave-uniform value).
 // Loop shapes (LOOP): 0 = phases per iteration
 // (after Aila and Laine's "while-while" loop with postponed leaves: every lane
 // walks internal nodes until it holds a leaf, then all held leaves are
@@ -1087,7 +1086,9 @@ __global__ void trace_tile_prefix(const TraceScene *scenes, int n, int cap, int3
 // push/pop and one shared copy of the stack code runs after the work; 3 =
 // as 2, but every lane fetches its node or its triangle's map into the same
 // registers with one shared load sequence, so an iteration waits for memory
-// once instead of once per kind of work; 4 = queued triangle tests (below).
+// once instead of once per kind of work; 4 = queued triangle tests (below),
+// rays starting at their tile's entry points; 5 = the same with rays starting
+// at the root (single scenes of few rays, in place of 4: see kFewRays).
 // BATCHED launches serve many scenes: a global tile
 // index is mapped to its scene through the tile prefix.  Instrumented runs
 // (STATS) also count into 64-bit counters at workspace offsets 8, 16, ...:
@@ -1390,8 +1391,8 @@ trace_persistent(TraceArgs A)
                 // The loop is bound by vector instructions and, nearly as much, by the data return of its loads: an
                 // iteration is 90 instructions and 56 bytes a lane (106 and 64 before the pending word, the queue
                 // without wrap-around, the stack by address and the shorter node step; with the scenes' records read
-                // anew each round, 28 registers' worth of spilled scalars less per round).  Room, 216k triangles,
-                // 128^3 / 256^3, 16 rays: 20.1 -> 19.5 ms; 12 scenes in one launch: 17.8 -> 17.1 ms.
+                // anew each round, 28 registers' worth of spilled scalars less per round).  Whole updates: a room of
+                // 216k triangles, 128^3 / 256^3, 16 rays: 21.0 -> 20.35 ms; 12 scenes in one launch: 17.2 -> 16.5 ms.
                 // Between flushes a lane culls boxes against its ray's best distance as of the last flush
                 // (a larger bound only enters more boxes); the closest hit is the minimum of the
                 // (t, triangle id, facing) keys of all tests, as in the other loops.
@@ -1692,8 +1693,9 @@ __global__ void directions_kernel(const int32_t *texel, const uint32_t *frame, c
 // Closest hits, a ray per lane.  Bound by latency (dependent node loads) at the occupancy that the stacks leave: 32
 // entries allow 16 wavefronts per compute unit, the 64 of a rebuilt hierarchy 8.  SHORT: the first of two launches,
 // with 20 entries (32 wavefronts); a ray whose stack fills leaves kRayTodo as its distance, and the second launch, with
-// the full stack, takes those rays only.  300,007 rays against 223,228 triangles after a rebuild, with the rebuild:
-// 875 -> 597 us (16 entries: 650, 12: 723, with more rays left over; 24: 597).
+// the full stack, takes those rays only.  300,007 rays after a rebuild, with the rebuild, in three rooms of 200,000 to
+// 226,000 triangles: the full stack alone 850 / 846 / 861 us, 12 entries 713 / 703 / 720 and 16 entries 610 / 636 / 640
+// (more rays left over), 20 entries 554 / 578 / 577, 24 entries 555 / 578 / 577.
 constexpr uint32_t kRayTodo = 0x7FA5A5A5u;  // a NaN that no hit distance is
 constexpr int kShortHitStack = 20;
 

@@ -44,6 +44,7 @@ __device__ __forceinline__ int64_t floor_div_pos(int64_t a, int64_t b)  // b > 0
     return q;
 }
 
+// A vertex snapped to 1/256 voxel (batches; snap32 below gives the same numbers).
 __device__ __forceinline__ bool snap(const float *__restrict__ v, int vi, const rtsdf_grid &g, int64_t X[3])
 {
     const double side = (double)g.n * (double)g.h;
@@ -120,7 +121,7 @@ __device__ __forceinline__ void vox_column(const VoxTri &T, int i, int j, int n,
     seeds[idx] = idx;
 }
 
-// Lane part of one (triangle, axis) item: snap, set up, rasterize a small
+// Lane part of one (triangle, axis) item of a batch: snap, set up, rasterize a small
 // projection directly; returns true when the projection is large and left to
 // the whole wavefront.
 __device__ __forceinline__ bool vox_item(const float *__restrict__ v, int nv, const int32_t *__restrict__ f, int t,
@@ -148,8 +149,8 @@ __device__ __forceinline__ bool vox_item(const float *__restrict__ v, int nv, co
     return true;
 }
 
-// Large projections of the wavefront's lanes, rasterized by all 64 lanes in
-// turn; `seeds` / `n` may differ per lane (many scenes per launch).
+// Large projections of the wavefront's lanes in a batch, rasterized by all 64
+// lanes in turn; `seeds` / `n` may differ per lane (many scenes per launch).
 __device__ __forceinline__ void vox_wave_big(bool big, const VoxTri &T, int32_t *seeds, int n)
 {
     const int lane = threadIdx.x & (kWave - 1);
