@@ -7,20 +7,21 @@
 // column covered when its centre is inside or on the projected triangle, and
 // the voxel holding the triangle's depth at that centre marked.
 //
-// Work mapping: a projection whose bounding box holds at most kSmallPixels
-// column centres is rasterized by one lane in 32-bit integers (three
-// projections a lane: a triangle's vertices are snapped once); larger ones by
-// a whole wavefront, and those of more than kWavePixels (room walls cover
-// whole faces of the grid) by the whole workgroup, in 64-bit integers.
-// Triangles are dealt to workgroups one by one, so the large projections of
-// consecutive triangles (the walls of a room come one after another) land in
-// different workgroups instead of queueing in one.
+// Work mapping: a lane takes a triangle (its vertices are snapped once), or in workgroups that are at most a quarter
+// full one of its three projections.  It rasterizes those whose bounding box holds at most kSmallPixels column centres,
+// in 32-bit integers, and lists the others in LDS beside the snapped vertices: projections of up to 32 voxels' extent
+// (32-bit integers) or kWavePixels columns (64-bit) go to the workgroup's wavefronts in turn, larger ones (room walls
+// cover whole faces of the grid) to the whole workgroup.
+// Consecutive triangles go to consecutive workgroups of one XCD: the large projections of consecutive triangles (the
+// walls of a room) land in different workgroups instead of queueing in one, and the cache lines that neighbouring
+// triangles share are read by one L2 (by consecutive workgroups of all XCDs, 1.0 M triangles without shared vertices
+// took 175 us at 256^3, now 74).
 //
-// Bound by the latency of its gathers and its largest projections: with the
-// fill of the seeds, 1.0 M triangles at 256^3 355 -> 151 us, 211 k at 128^3
-// 108 -> 48 us, 1,880 large ones at 256^3 432 -> 54 us, 322 at 32^3 16 -> 11 us
-// (against one lane per (triangle, axis) in 64-bit integers, which snapped each
-// vertex three times and left a wall's 65,536 columns to one wavefront).
+// Bound by the latency of its gathers and its largest projections.  With the fill of the seeds, against one lane per
+// (triangle, axis) in 64-bit integers whose larger projections queue in its wavefront: a room of 1.07 M triangles at
+// 256^3 355 -> 109 us, one of 69,760 at 256^3 368 -> 69 and at 128^3 107 -> 28, soups of 1.0 M small triangles at 32^3
+// 105 -> 59, of 300,000 of about 26 columns at 256^3 299 -> 246, of 20,000 of about 160 at 128^3 126 -> 45, 12 that cover
+// the grid at 256^3 3,070 -> 69.
 #include <algorithm>
 #include <cmath>
 
@@ -178,12 +179,15 @@ __device__ __forceinline__ void vox_wave_big(bool big, const VoxTri &T, int32_t 
     }
 }
 
-// Threads per workgroup and fewest workgroups (four for each compute unit, so a small mesh's large projections do not
-// share one).  With 1024 threads a million triangles at 256^3 take 175 us, with 512 151, with 256 146, but 1,880 large
-// ones 54, 54 and 68; four consecutive triangles per workgroup (their faces in one cache line) 208 and 111.
+// Threads per workgroup, and fewest workgroups: enough that a small mesh's large projections do not share one, few
+// enough that the start of mostly empty ones does not show (with 1024, 20,000 small triangles at 128^3 take 14.0 us
+// instead of 11.9, but the room of 69,760 at 256^3 60 instead of 69, and with 512 none of the sizes above is slower than
+// with a lane per axis).
 constexpr int kVoxThreads = 512;
-constexpr int kVoxBlocks = 1024;
-constexpr int kWavePixels = 512;   // largest projection a single wavefront takes
+constexpr int kVoxBlocks = 512;
+// triangles of a workgroup at most whose axes go to different wavefronts (20,000 small ones at 256^3 36 -> 28 us)
+constexpr int kVoxSplit = 2 * kWave;
+constexpr int kWavePixels = 512;   // largest projection with long edges that a single wavefront takes
 constexpr int kSmallExtent = 8192;  // 32 voxels, also outside the grid: edge functions below 2^28 in 32 bits
 
 // A vertex snapped to 1/256 voxel; POW2: the voxel size is a power of two, so its inverse is exact and multiplies.
@@ -200,62 +204,84 @@ __device__ __forceinline__ bool snap32(const float *__restrict__ v, const rtsdf_
     return true;
 }
 
-// One projection by one lane.  Returns true when it is left to more lanes: many columns, or long edges.
-__device__ __forceinline__ bool vox_small(const int32_t (&X)[3][3], int axis, int n, int32_t *__restrict__ seeds)
+// A projection: the vertices' coordinates in its plane and their depths, and the columns of its box in the grid.
+struct VoxProj {
+    int32_t x[3], y[3], z[3];
+    int i0, i1, j0, j1;
+    bool edges32;  // short enough for edge functions in 32 bits
+};
+
+__device__ __forceinline__ bool vox_box(VoxProj &P, int n)  // false if the box holds no column centre
 {
-    const int e1 = (axis + 1) % 3, e2 = (axis + 2) % 3;
-    const int32_t x0 = X[0][e1], x1 = X[1][e1], x2 = X[2][e1], y0 = X[0][e2], y1 = X[1][e2], y2 = X[2][e2];
-    const int32_t minx = min(x0, min(x1, x2)), maxx = max(x0, max(x1, x2));
-    const int32_t miny = min(y0, min(y1, y2)), maxy = max(y0, max(y1, y2));
+    const int32_t minx = min(P.x[0], min(P.x[1], P.x[2])), maxx = max(P.x[0], max(P.x[1], P.x[2]));
+    const int32_t miny = min(P.y[0], min(P.y[1], P.y[2])), maxy = max(P.y[0], max(P.y[1], P.y[2]));
     // column centre 256 i + 128 within [min, max]
-    const int i0 = max((minx + 127) >> 8, 0), i1 = min((maxx - 128) >> 8, n - 1);
-    const int j0 = max((miny + 127) >> 8, 0), j1 = min((maxy - 128) >> 8, n - 1);
-    if (i0 > i1 || j0 > j1) return false;
-    if (maxx - minx > kSmallExtent || maxy - miny > kSmallExtent || (i1 - i0 + 1) * (j1 - j0 + 1) > kSmallPixels)
-        return true;
-    int32_t area = (x1 - x0) * (y2 - y0) - (y1 - y0) * (x2 - x0);
-    if (area == 0) return false;
-    // edge functions times the orientation: all >= 0 inside or on the boundary, their sum |area|
-    const int32_t s = area < 0 ? -1 : 1;
-    area *= s;
-    const double den = (double)area * 256.0, inv = 1.0 / den;
-    const double z0 = X[0][axis], z1 = X[1][axis], z2 = X[2][axis];
-    const int sx = axis == 0 ? n : axis == 1 ? n * n : 1, sy = axis == 0 ? n * n : axis == 1 ? 1 : n;
-    const int sz = axis == 0 ? 1 : axis == 1 ? n : n * n;
-    for (int j = j0; j <= j1; ++j) {
-        const int32_t cy = 256 * j + 128;
-        for (int i = i0; i <= i1; ++i) {
-            const int32_t cx = 256 * i + 128;
-            const int32_t w0 = s * ((x2 - x1) * (cy - y1) - (y2 - y1) * (cx - x1));
-            const int32_t w1 = s * ((x0 - x2) * (cy - y2) - (y0 - y2) * (cx - x2));
-            const int32_t w2 = area - w0 - w1;
-            if ((w0 | w1 | w2) < 0) continue;
-            // depth num / den, every product and sum below 2^53: exact
-            const double num = (double)w0 * z0 + (double)w1 * z1 + (double)w2 * z2;
-            double L = floor(num * inv);  // off by at most one
-            const double rem = fma(-L, den, num);
-            if (rem < 0.0) L -= 1.0;
-            else if (rem >= den) L += 1.0;
-            if (num == (double)n * den) L = (double)(n - 1);
-            if (L < 0.0 || L >= (double)n) continue;
-            const int idx = (int)L * sz + i * sx + j * sy;
-            seeds[idx] = idx;
-        }
-    }
-    return false;
+    P.i0 = max((minx + 127) >> 8, 0);
+    P.i1 = min((maxx - 128) >> 8, n - 1);
+    P.j0 = max((miny + 127) >> 8, 0);
+    P.j1 = min((maxy - 128) >> 8, n - 1);
+    P.edges32 = maxx - minx <= kSmallExtent && maxy - miny <= kSmallExtent;
+    return P.i0 <= P.i1 && P.j0 <= P.j1;
 }
 
-// One projection by many lanes: lane (lx, ly) of a block of 64 x ny columns.
-__device__ __forceinline__ void vox_wide(const int32_t (&X32)[3][3], int axis, int n, int lx, int ly, int ny,
-                                         int32_t *__restrict__ seeds)
+// What the columns of a projection share, in 32-bit integers; false if its area is zero.
+struct VoxEdges {
+    int32_t area, s;  // edge functions times the orientation s: all >= 0 inside or on the boundary, their sum the area
+    double den, inv;
+    int sx, sy, sz;
+};
+
+__device__ __forceinline__ bool vox_edges(const VoxProj &P, int axis, int n, VoxEdges &E)
 {
-    int64_t X[3][3];
-    for (int k = 0; k < 3; ++k)
-        for (int a = 0; a < 3; ++a) X[k][a] = X32[k][a];
-    VoxTri T;
-    if (!vox_setup(X, axis, n, T)) return;
-    for (int j = T.j0 + ly; j <= T.j1; j += ny)
-        for (int i = T.i0 + lx; i <= T.i1; i += kWave) vox_column(T, i, j, n, seeds);
+    E.area = (P.x[1] - P.x[0]) * (P.y[2] - P.y[0]) - (P.y[1] - P.y[0]) * (P.x[2] - P.x[0]);
+    if (E.area == 0) return false;
+    E.s = E.area < 0 ? -1 : 1;
+    E.area *= E.s;
+    E.den = (double)E.area * 256.0;
+    E.inv = 1.0 / E.den;
+    E.sx = axis == 0 ? n : axis == 1 ? n * n : 1;
+    E.sy = axis == 0 ? n * n : axis == 1 ? 1 : n;
+    E.sz = axis == 0 ? 1 : axis == 1 ? n : n * n;
+    return true;
+}
+
+__device__ __forceinline__ void vox_column32(const VoxProj &P, const VoxEdges &E, int i, int j, int n,
+                                             int32_t *__restrict__ seeds)
+{
+    const int32_t cx = 256 * i + 128, cy = 256 * j + 128;
+    const int32_t w0 = E.s * ((P.x[2] - P.x[1]) * (cy - P.y[1]) - (P.y[2] - P.y[1]) * (cx - P.x[1]));
+    const int32_t w1 = E.s * ((P.x[0] - P.x[2]) * (cy - P.y[2]) - (P.y[0] - P.y[2]) * (cx - P.x[2]));
+    const int32_t w2 = E.area - w0 - w1;
+    if ((w0 | w1 | w2) < 0) return;
+    // depth num / den, every product and sum below 2^53: exact
+    const double num = (double)w0 * (double)P.z[0] + (double)w1 * (double)P.z[1] + (double)w2 * (double)P.z[2];
+    double L = floor(num * E.inv);  // off by at most one
+    const double rem = fma(-L, E.den, num);
+    if (rem < 0.0) L -= 1.0;
+    else if (rem >= E.den) L += 1.0;
+    if (num == (double)n * E.den) L = (double)(n - 1);
+    if (L < 0.0 || L >= (double)n) return;
+    const int idx = (int)L * E.sz + i * E.sx + j * E.sy;
+    seeds[idx] = idx;
+}
+
+// The columns of a projection's box by lane `first` of `step` (a multiple of kWave): row by row, and where the rows are
+// long a row by the lanes of one wavefront, which share the row's products (12 triangles of 256^2 columns: 70 against 91
+// us).
+template <typename F>
+__device__ __forceinline__ void vox_columns(int i0, int i1, int j0, int j1, int first, int step, F column)
+{
+    const int w = i1 - i0 + 1, npix = w * (j1 - j0 + 1);
+    if (w >= kWave) {
+        for (int j = j0 + first / kWave; j <= j1; j += step / kWave)
+            for (int i = i0 + first % kWave; i <= i1; i += kWave) column(i, j);
+        return;
+    }
+    const float inv_w = 1.0f / (float)w;
+    for (int p = first; p < npix; p += step) {
+        const int r = (int)(((float)p + 0.5f) * inv_w);  // p / w: below 256, half a column from any other
+        column(i0 + p - r * w, j0 + r);
+    }
 }
 
 template <bool POW2>
@@ -263,66 +289,103 @@ __global__ void __launch_bounds__(kVoxThreads) voxelize_kernel(const float *__re
                                                                const int32_t *__restrict__ f, int nt, rtsdf_grid g,
                                                                double inv_h, int32_t *__restrict__ seeds)
 {
-    __shared__ uint32_t big[3 * kVoxThreads];  // projections left to the workgroup: thread << 2 | axis
-    __shared__ uint32_t nbig;
-    if (threadIdx.x == 0) nbig = 0u;
+    // projections left to a wavefront (from the front) and to the workgroup (from the back): thread << 2 | axis, and
+    // those threads' snapped vertices (read from LDS, so that a projection doesn't wait for gathers of its own)
+    constexpr int kList = 3 * kVoxThreads;
+    __shared__ uint32_t list[kList], ends[2];
+    __shared__ int32_t snapped[kVoxThreads][9];
+    if (threadIdx.x < 2) ends[threadIdx.x] = 0u;
     __syncthreads();
-    const int lane = threadIdx.x & (kWave - 1);
-    const auto tri_of = [&](uint32_t thread) { return (int64_t)thread * gridDim.x + blockIdx.x; };
-    const auto load = [&](int64_t t, int32_t (&X)[3][3]) {  // 0, or the error bit
-        for (int k = 0; k < 3; ++k) {
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // consecutive triangles to consecutive workgroups of one XCD (workgroups go to the 8 XCDs in turn), a sparse
+    // workgroup's triangles to all of its wavefronts, and of a quarter full one the three axes to three wavefronts
+    const uint32_t xcd = blockIdx.x & 7u, per = gridDim.x >> 3;
+    const uint32_t place = xcd * per + min(xcd, gridDim.x & 7u) + (blockIdx.x >> 3);
+    const bool split = (nt + (int)gridDim.x - 1) / (int)gridDim.x <= kVoxSplit;
+    const int64_t t = (split && wave >= 6 ? (int64_t)nt : 0) +
+                      (int64_t)(split ? lane * 2 + wave / 3 : lane * (kVoxThreads / kWave) + wave) * gridDim.x + place;
+    int32_t X[3][3];
+    uint32_t err = 0;
+    if (t < nt) {
+        for (int k = 0; k < 3 && !err; ++k) {
             const int vi = f[3 * t + k];
-            if (vi < 0 || vi >= nv) return (uint32_t)RTSDF_ERR_FACE_INDEX;
+            if (vi < 0 || vi >= nv) err = RTSDF_ERR_FACE_INDEX;
             X[k][0] = vi;
         }
-        for (int k = 0; k < 3; ++k)
-            if (!snap32<POW2>(v + 3 * (int64_t)X[k][0], g, inv_h, X[k])) return (uint32_t)RTSDF_ERR_VERTEX_RANGE;
-        return 0u;
-    };
-    const int64_t t = tri_of(threadIdx.x);
-    int32_t X[3][3];
-    uint32_t wide = 0;  // axes left to the wavefront
-    if (t < nt) {
-        const uint32_t err = load(t, X);
+        for (int k = 0; k < 3 && !err; ++k)
+            if (!snap32<POW2>(v + 3 * (int64_t)X[k][0], g, inv_h, X[k])) err = RTSDF_ERR_VERTEX_RANGE;
         if (err) raise_error(err);
-        else
-            for (int axis = 0; axis < 3; ++axis)
-                if (vox_small(X, axis, g.n, seeds)) {
-                    // columns of the box in the grid, as above
-                    const int e1 = (axis + 1) % 3, e2 = (axis + 2) % 3;
-                    const int w = min((max(X[0][e1], max(X[1][e1], X[2][e1])) - 128) >> 8, g.n - 1) -
-                                  max((min(X[0][e1], min(X[1][e1], X[2][e1])) + 127) >> 8, 0) + 1;
-                    const int h = min((max(X[0][e2], max(X[1][e2], X[2][e2])) - 128) >> 8, g.n - 1) -
-                                  max((min(X[0][e2], min(X[1][e2], X[2][e2])) + 127) >> 8, 0) + 1;
-                    if (w * h <= kWavePixels) wide |= 1u << axis;
-                    else big[atomicAdd(&nbig, 1u)] = threadIdx.x << 2 | (uint32_t)axis;
-                }
     }
-    // the wavefront's projections, one after another
-    for (int axis = 0; axis < 3; ++axis) {
-        uint64_t pending = __ballot((wide >> axis & 1u) != 0u);
-        while (pending) {
-            const int src = __ffsll((unsigned long long)pending) - 1;
-            pending &= pending - 1;
-            int32_t B[3][3];
-            for (int k = 0; k < 3; ++k)
-                for (int a = 0; a < 3; ++a) B[k][a] = __builtin_amdgcn_readlane(X[k][a], src);
-            int64_t B64[3][3];
-            for (int k = 0; k < 3; ++k)
-                for (int a = 0; a < 3; ++a) B64[k][a] = B[k][a];
-            VoxTri T;
-            if (!vox_setup(B64, axis, g.n, T)) continue;
-            const int w = T.i1 - T.i0 + 1, npix = w * (T.j1 - T.j0 + 1);
-            for (int p = lane; p < npix; p += kWave) vox_column(T, T.i0 + p % w, T.j0 + p / w, g.n, seeds);
+    if (t < nt && !err) {
+        bool left = false;
+#pragma unroll
+        for (int axis = 0; axis < 3; ++axis) {
+            if (split && wave % 3 != axis) continue;
+            VoxProj P;
+            for (int k = 0; k < 3; ++k) {
+                P.x[k] = X[k][(axis + 1) % 3];
+                P.y[k] = X[k][(axis + 2) % 3];
+                P.z[k] = X[k][axis];
+            }
+            if (!vox_box(P, g.n)) continue;
+            const int npix = (P.i1 - P.i0 + 1) * (P.j1 - P.j0 + 1);
+            if (P.edges32 && npix <= kSmallPixels) {
+                VoxEdges E;
+                if (!vox_edges(P, axis, g.n, E)) continue;
+                for (int j = P.j0; j <= P.j1; ++j)
+                    for (int i = P.i0; i <= P.i1; ++i) vox_column32(P, E, i, j, g.n, seeds);
+                continue;
+            }
+            left = true;
+            const uint32_t e = threadIdx.x << 2 | (uint32_t)axis;
+            if (P.edges32 || npix <= kWavePixels) list[atomicAdd(&ends[0], 1u)] = e;
+            else list[kList - 1 - atomicAdd(&ends[1], 1u)] = e;
         }
+        if (left)
+            for (int k = 0; k < 9; ++k) snapped[threadIdx.x][k] = X[k / 3][k % 3];
     }
     __syncthreads();
-    const uint32_t n = nbig;
-    for (uint32_t q = 0; q < n; ++q) {
-        const uint32_t e = big[q];
-        int32_t B[3][3];
-        (void)load(tri_of(e >> 2), B);  // (checked by its own lane)
-        vox_wide(B, (int)(e & 3u), g.n, lane, threadIdx.x >> 6, kVoxThreads / kWave, seeds);
+    const auto get = [&](uint32_t e, VoxProj &P) {
+        const int32_t *S = snapped[e >> 2];
+        const int axis = (int)(e & 3u), e1 = axis == 2 ? 0 : axis + 1, e2 = axis == 0 ? 2 : axis - 1;
+        for (int k = 0; k < 3; ++k) {
+            P.x[k] = __builtin_amdgcn_readfirstlane(S[3 * k + e1]);
+            P.y[k] = __builtin_amdgcn_readfirstlane(S[3 * k + e2]);
+            P.z[k] = __builtin_amdgcn_readfirstlane(S[3 * k + axis]);
+        }
+        return axis;
+    };
+    const auto wide = [&](const VoxProj &P, int axis, int first, int step) {  // in 64 bits
+        int64_t X64[3][3];
+        for (int k = 0; k < 3; ++k) {
+            X64[k][0] = P.x[k];
+            X64[k][1] = P.y[k];
+            X64[k][2] = P.z[k];
+        }
+        VoxTri T;
+        if (!vox_setup(X64, 2, g.n, T)) return;
+        T.axis = axis;
+        vox_columns(T.i0, T.i1, T.j0, T.j1, first, step, [&](int i, int j) { vox_column(T, i, j, g.n, seeds); });
+    };
+    // the wavefronts' projections, dealt out over all of the workgroup's (the triangles of a small mesh are all in its
+    // first wavefront)
+    for (uint32_t q = wave; q < ends[0]; q += kVoxThreads / kWave) {
+        VoxProj P;
+        const int axis = get(__builtin_amdgcn_readfirstlane(list[q]), P);
+        (void)vox_box(P, g.n);
+        if (P.edges32) {
+            VoxEdges E;
+            if (!vox_edges(P, axis, g.n, E)) continue;
+            vox_columns(P.i0, P.i1, P.j0, P.j1, lane, kWave,
+                        [&](int i, int j) { vox_column32(P, E, i, j, g.n, seeds); });
+        } else {
+            wide(P, axis, lane, kWave);
+        }
+    }
+    for (uint32_t q = 0; q < ends[1]; ++q) {
+        VoxProj P;
+        const int axis = get(__builtin_amdgcn_readfirstlane(list[kList - 1 - q]), P);
+        wide(P, axis, threadIdx.x, kVoxThreads);
     }
 }
 
