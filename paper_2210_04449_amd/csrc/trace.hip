@@ -1149,7 +1149,16 @@ trace_persistent(TraceArgs A)
 
     // wave-uniform context state: -1 free, else rays not yet finished | texels << 16; and the scene (batches).  Two of
     // them in two-level scenes too, where a ray keeps its world direction in LDS: a room of 120 objects with rigid parts,
-    // 256^3, 5 rays: 8,980 -> 8,300 us (lanes with work 0.69 -> 0.79 of lane-iterations)
+    // 256^3, 5 rays: 8,980 -> 8,300 us (lanes with work 0.69 -> 0.79 of lane-iterations).  There a launch of few tiles
+    // uses one: asking for a next tile with rays in flight, when there is mostly none, and handing tiles of one
+    // wavefront of rays out in pieces cost more than lanes that wait (traces of rigid parts at 128^3, 1 ray, 0.7 tiles
+    // per wavefront: 176 us with two, 161 with one; at 64^3 in tiles of 16 texels 174 and 145; 2 rays, 0.7 tiles: 232
+    // and 222; with 1 ray and 2.25 or 3.5 tiles per wavefront of a room's parts two are faster, 386 against 389 and 630
+    // against 656, at 2.7 of the lone parts one, 394 against 377).
+    // (kept as the sign of the number of tiles: one more scalar over the traversal costs 0.4 %)
+    const int ntiles = INST && all_tiles <= (int)gridDim.x * kTraceWaves * (one_tt * A.one.rays <= kWave ? 2 : 1)
+                           ? -all_tiles
+                           : all_tiles;
     int cstate[2] = {-1, -1}, cscene[2] = {0, 0};
     int cur = 0, pool = 0, nrays = 0;  // the context rays are handed out from
     uint32_t rdiv = 0;                 // its q / R multiplier (below)
@@ -1175,10 +1184,10 @@ trace_persistent(TraceArgs A)
                 int g = 0;
                 if (lane == 0) g = atomicAdd(A.cursor, 1);
                 g = __builtin_amdgcn_readlane(g, 0);  // a wave-uniform (scalar) value
-                gnext = g < all_tiles ? g : -1;
+                gnext = g < (INST ? abs(ntiles) : ntiles) ? g : -1;
             }
             const int sn = gnext >= 0 && BATCHED ? scene_of(gnext) : 0;
-            if (gnext >= 0 && (!any_busy || !BATCHED || sn == cscene[cur])) {
+            if (gnext >= 0 && (!any_busy || ((!INST || ntiles > 0) && (!BATCHED || sn == cscene[cur])))) {
                 const int c = cur ^ 1, g = gnext;
                 gnext = -2;
                 const TraceScene &P = BATCHED ? A.scenes[sn] : A.one;
@@ -1268,7 +1277,7 @@ trace_persistent(TraceArgs A)
         {
             // refill rounds go on while this tile has rays or the next one can start before every lane is
             // done; otherwise every lane finishes first
-            const bool early = cstate[cur ^ 1] < 0 &&
+            const bool early = (!INST || ntiles > 0) && cstate[cur ^ 1] < 0 &&
                                (gnext == -2 || (gnext >= 0 && (!BATCHED || scene_of(gnext) == cscene[cur])));
             const int refill_at = __builtin_amdgcn_readfirstlane(pool < nrays || early ? REFILL : kWave);
             if (STATS) st_drains += refill_at == kWave && gnext != -1;  // every lane finishes before the next tile
