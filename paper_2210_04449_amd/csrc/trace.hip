@@ -1700,7 +1700,7 @@ __global__ void directions_kernel(const int32_t *texel, const uint32_t *frame, c
 }
 
 // Closest hits, a ray per lane.  Bound by latency (dependent node loads) at the occupancy that the stacks leave: 32
-// entries allow 16 wavefronts per compute unit, the 64 of a rebuilt hierarchy 8.  SHORT: the first of two launches,
+// entries allow 16 wavefronts per compute unit, the 64 of a rebuilt hierarchy 8.  kHitsShort: the first of two launches,
 // with 20 entries (32 wavefronts); a ray whose stack fills leaves kRayTodo as its distance, and the second launch, with
 // the full stack, takes those rays only.  300,007 rays after a rebuild, with the rebuild, in three rooms of 200,000 to
 // 226,000 triangles: the full stack alone 850 / 846 / 861 us, 12 entries 713 / 703 / 720 and 16 entries 610 / 636 / 640
@@ -1708,16 +1708,18 @@ __global__ void directions_kernel(const int32_t *texel, const uint32_t *frame, c
 constexpr uint32_t kRayTodo = 0x7FA5A5A5u;  // a NaN that no hit distance is
 constexpr int kShortHitStack = 20;
 
-template <int SD, bool SHORT>
+enum HitsPass { kHitsAll, kHitsShort, kHitsRest };  // (one launch of all rays has no test for those left over)
+
+template <int SD, HitsPass PASS>
 __global__ void __launch_bounds__(256) closest_hits_kernel(BvhView S, int nt, const float *__restrict__ o,
                                                            const float *__restrict__ d, int n, float *t_out,
-                                                           int32_t *tri_out, int32_t *front_out, bool todo_only)
+                                                           int32_t *tri_out, int32_t *front_out)
 {
     __shared__ int stack_mem[4 * SD * kWave];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int *stk = stack_mem + wave * SD * kWave + lane;
-    if (i >= n || (todo_only && __float_as_uint(t_out[i]) != kRayTodo)) return;
+    if (i >= n || (PASS == kHitsRest && __float_as_uint(t_out[i]) != kRayTodo)) return;
     RaySetup R;
     ray_setup(o[3 * i], o[3 * i + 1], o[3 * i + 2], d[3 * i], d[3 * i + 1], d[3 * i + 2], R);
     float tbest = __builtin_inff();
@@ -1725,7 +1727,7 @@ __global__ void __launch_bounds__(256) closest_hits_kernel(BvhView S, int nt, co
     bool front = false;
     while (node != kDone) {
         trav_step(S, R, node, sp, stk, kWave, tbest, ibest, front);
-        if (SHORT && sp >= SD) {
+        if (PASS == kHitsShort && sp >= SD) {
             t_out[i] = __uint_as_float(kRayTodo);
             return;
         }
@@ -2080,15 +2082,19 @@ extern "C" int rtsdf_closest_hits(const rtsdf_scene *scene, const float *origins
     // short stacks first where the full ones leave no room for all rays at once (64 entries, 140,000 rays: 382 -> 265
     // us; 100,000: 248 -> 267; 32 entries, 320,000 rays: 357 -> 258; 250,000: 223 -> 236)
     const bool two = (int64_t)n * full * 4 > kChipLds && sd > kShortHitStack;
+    const auto launch = [&](auto kernel) {
+        kernel<<<g, b, 0, s>>>(S, scene->nt, origins, dirs, n, t_out, tri_out, front_out);
+    };
     if (two) {
-        closest_hits_kernel<kShortHitStack, true>
-            <<<g, b, 0, s>>>(S, scene->nt, origins, dirs, n, t_out, tri_out, front_out, false);
+        launch(closest_hits_kernel<kShortHitStack, kHitsShort>);
         RTSDF_CHECK_LAUNCH();
+        if (full == 32) launch(closest_hits_kernel<32, kHitsRest>);
+        else launch(closest_hits_kernel<64, kHitsRest>);
+    } else if (full == 32) {
+        launch(closest_hits_kernel<32, kHitsAll>);
+    } else {
+        launch(closest_hits_kernel<64, kHitsAll>);
     }
-    if (full == 32)
-        closest_hits_kernel<32, false><<<g, b, 0, s>>>(S, scene->nt, origins, dirs, n, t_out, tri_out, front_out, two);
-    else
-        closest_hits_kernel<64, false><<<g, b, 0, s>>>(S, scene->nt, origins, dirs, n, t_out, tri_out, front_out, two);
     RTSDF_CHECK_LAUNCH();
     return RTSDF_OK;
 }
